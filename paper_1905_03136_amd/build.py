@@ -29,11 +29,20 @@ CFLAGS = [
     # keep the compiler from forming packed FP32 instructions (not used here anyway)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-but-set-variable",
+    "-Wno-inline-asm",  # m0 in a clobber list
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 
+# The kernels that stage their rows in LDS: FP64 matrix-core results in
+# architectural registers.  With C and D in accumulation registers a 16x16x4
+# product takes 104 (two waves a SIMD) to 141 cycles (one) instead of 65:
+# register-only loops reach 38-52 and 77 TF/s.
+STAGE_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+
 # headers every unit includes; the C ABI header only the hand-written units
 HEADERS = [os.path.join(CSRC, h) for h in ("tsg_device.hpp", "tsg_kernels.hpp", "tsg_registry.hpp")]
+# header of the units that hold kernels staging their rows in LDS
+STAGE_HEADER = os.path.join(CSRC, "tsg_stage.hpp")
 ABI_HEADER = os.path.join(ROOT, "include", "tsgemm.h")
 TUNE_LIB = os.path.join(HERE, "libtsgemm_tune.so")
 # builds of other variant sets (the autotuner's libraries): generated sources
@@ -191,12 +200,19 @@ def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, l
     jobs = jobs or min(8, os.cpu_count() or 1)
     # objects built with other flags are stale (the flags are kept beside them)
     stamp = os.path.join(OBJD, "flags.txt")
-    flags = " ".join([HIPCC] + CFLAGS + list(extra_flags))
+    flags = " ".join([HIPCC] + CFLAGS + STAGE_FLAGS + list(extra_flags))
     same_flags = os.path.exists(stamp) and open(stamp).read() == flags
+
+    def staged(s):
+        with open(s) as f:
+            return '#include "tsg_stage.hpp"' in f.read()
+
+    def deps(s):
+        return [s] + HEADERS + ([STAGE_HEADER] if staged(s) else []) + ([] if s in units else [ABI_HEADER])
 
     def compile_all(sources, what):
         todo = [(s, obj_of[s]) for s in sources
-                if not same_flags or _stale(obj_of[s], [s] + HEADERS + ([] if s in units else [ABI_HEADER]))
+                if not same_flags or _stale(obj_of[s], deps(s))
                 or (s in units and not (os.path.exists(obj_of[s] + SPILLS) and
                                         os.path.exists(obj_of[s] + RESOURCES)))]
         if not todo:
@@ -205,7 +221,8 @@ def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, l
             print("[build] compiling %d of %d %s for %s (%d variants), %d jobs"
                   % (len(todo), len(sources), what, ARCH, len(variants), jobs), flush=True)
         with cf.ThreadPoolExecutor(jobs) as ex:
-            for done in ex.map(lambda so: _compile(so[0], so[1], list(extra_flags), so[0] in units), todo):
+            for done in ex.map(lambda so: _compile(so[0], so[1], list(extra_flags) + (STAGE_FLAGS if staged(so[0]) else []),
+                                                       so[0] in units), todo):
                 if verbose:
                     print("[build]   %s" % os.path.relpath(done, ROOT), flush=True)
 

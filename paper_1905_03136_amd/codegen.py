@@ -87,81 +87,19 @@ def candidates(op, dt, M, N):
     out = _candidates(op, dt, M, N)
     if is_f32(dt):
         out = [c for c in out if c["kind"] != "valu" and not c.get("VA")]
-    else:
-        out += _lds_candidates(op, dt, M, N)
     return out
 
 
 LDS_BYTES = 160 * 1024  # LDS of one compute unit (gfx950)
 
 
-def _lds_candidates(op, dt, M, N):
-    """TSMTTSM with the rows staged in LDS by direct loads (tsmttsm_lds) for
-    widths above 16: WM x WN waves of MB x NB blocks of 16 x 16 cover C,
-    stages of RT rows, two stages in LDS.  Register model in doubles per
-    lane: accumulators plus the operands of one stage; two blocks per
-    compute unit (OCC = 2) where their LDS fits."""
-    out = []
-    if op != "tsmttsm" or (M <= 16 and N <= 16):
-        return out
-    cplx = DTYPES[dt][1]
-    cw = 2 if cplx else 1
-    # Real odd widths: with K M odd the last element of A shares its 16-byte
-    # load with the 8 bytes past the end, and the clamp that keeps that load
-    # inside the matrix would move the element (the autotuner's exact-product
-    # gate rejected these kernels); complex elements are 16 bytes each.
-    if not cplx and (M % 2 or N % 2):
-        return out
-    mbt, nbt = _ceil(M, 16), _ceil(N, 16)
-    for wm in range(1, 9):
-        for wn in range(1, 9):
-            wpb = wm * wn
-            if wpb < 2 or wpb > 8 or wm > mbt or wn > nbt:
-                continue
-            mb, nb = _ceil(mbt, wm), _ceil(nbt, wn)
-            if (wm - 1) * mb >= mbt or (wn - 1) * nb >= nbt:
-                continue  # a wave without a block of C
-            for g3 in ((0, 1) if cplx else (0,)):
-                acc = mb * nb * 4 * (3 if g3 else cw)
-                if acc > 64:
-                    continue
-                for rt in (16, 32, 64):
-                    lds = 2 * (_ceil(rt * M * cw, 128) + _ceil(rt * N * cw, 128)) * 128 * 8
-                    if lds > LDS_BYTES:
-                        continue
-                    # IL: operand reads of a stage all at once (0) or IL steps
-                    # ahead of the products (then only IL + 1 steps of
-                    # operands are live)
-                    for il in (0, 1, 2):
-                        steps = rt // 4 if il == 0 else min(il + 1, rt // 4)
-                        if il and il + 1 > rt // 4:
-                            continue
-                        ops = steps * (mb + nb) * cw
-                        for occ in (1, 2, 3, 4):
-                            waves = occ * wpb
-                            # the waves of a CU spread evenly over its four SIMDs, at most
-                            # three per SIMD, and the register model fits that many
-                            if waves % 4 or waves > 12 or occ * lds > LDS_BYTES:
-                                continue
-                            if acc + ops > (104 if waves <= 8 else 80):
-                                continue
-                            c = dict(kind="lds", MB=mb, NB=nb, WM=wm, WN=wn, RT=rt, WPB=wpb)
-                            if occ > 1:
-                                c["OCC"] = occ
-                            if g3:
-                                c["G3"] = 1
-                            if il:
-                                c["IL"] = il
-                            out.append(c)
-    return out
-
-
 def _lds32_candidates(op, dt, M, N):
     """Binary32-arithmetic TSMTTSM with the rows staged in LDS
-    (tsmttsm_lds_a32): as _lds_candidates, stages of 16 or 32 rows (one
-    binary32 stretch is 32 rows), rows of whole 16-byte loads.  Register
-    model in binary64 units per lane: binary64 sums, binary32 stretch sums
-    and live operands (binary32: half a unit each)."""
+    (tsmttsm_lds_a32) for widths above 16: WM x WN waves of MB x NB blocks of
+    16 x 16 cover C, two stages of 16 or 32 rows in LDS (one binary32 stretch
+    is 32 rows), rows of whole 16-byte loads.  Register model in binary64
+    units per lane: binary64 sums, binary32 stretch sums and live operands
+    (binary32: half a unit each)."""
     out = []
     if op != "tsmttsm" or (M <= 16 and N <= 16):
         return out
@@ -687,6 +625,128 @@ def generic_variants(tuned_path=None):
     return out
 
 
+def stage_config(dt, wm, quads, sym=False, gauss=False, RT=0, NS=2, KG=1, OCC=2):
+    """Configuration of the TSMTTSM kernel that stages its rows in LDS
+    (tsmttsm_stage) for wm blocks of 16 columns of the wider matrix (one a
+    wave) and `quads` groups of 4 columns of the narrower one: KG row groups
+    of wm waves, stages of RT rows, NS of them, OCC waves a SIMD at least."""
+    if wm == 3:
+        KG = 4
+    if not RT:
+        # stages of 16 to 32 KB, two of them
+        RT = 4 * KG
+        while 2 * RT * stage_row(dt, wm, quads, sym) <= (16384 if wm == 2 else 32768) and RT < 64:
+            RT *= 2
+    c = dict(kind="stage", WM=wm, NB=wm // 2 + 1 if sym else quads // 4, NQ=0 if sym else quads % 4, RT=RT,
+             NS=NS, KG=KG, WPB=wm * KG, OCC=OCC)
+    if gauss:
+        c["G3"] = 1
+    if sym:
+        c["SYM"] = 1
+    return c
+
+
+def stage_fold(dt, c):
+    """LDS bytes of the sum over row groups of a configuration: one group's
+    accumulators (the three-product form's are combined before)."""
+    return 0 if c["KG"] == 1 else c["WM"] * (4 * c["NB"] + c["NQ"]) * (2 if DTYPES[dt][1] else 1) * 64 * 8
+
+
+def stage_row(dt, wm, quads, sym):
+    """Bytes of a stage's row at the class's largest widths."""
+    es = (2 if DTYPES[dt][1] else 1) * (4 if is_f32(dt) else 8)
+    return (16 * wm + (0 if sym else 4 * quads)) * es
+
+
+def stage_candidates(dt, wm, quads, sym=False, gauss=False):
+    """Configurations the autotuner times for one class: every stage height,
+    count of stages and row groups whose LDS and waves fit a compute unit,
+    with enough bytes in flight and the waves of a block spread evenly over
+    the four SIMDs (a block's waves start at the first SIMD: blocks of three
+    leave the fourth idle, 45 instead of 60 TF/s at complex 48 x 48, so three
+    column blocks go with four row groups)."""
+    out = []
+    row = stage_row(dt, wm, quads, sym)
+    pieces = lambda cols, rt: -(-cols * row // (16 * wm + (0 if sym else 4 * quads)) * rt // 1024)  # noqa: E731
+    for rt in (8, 16, 32, 64):
+        for ns in (2, 3):
+            for kg in ((4,) if wm == 3 else (1, 2, 4) if wm == 2 else (1, 2, 3)):
+                waves = wm * kg
+                st = (pieces(16 * wm, rt) + (0 if sym else pieces(4 * quads, rt))) * 1024
+                if rt % (4 * kg):
+                    continue
+                lds = max(st * ns + 1024, stage_fold(dt, stage_config(dt, wm, quads, sym, gauss, rt, ns, kg)))
+                if lds > LDS_BYTES:
+                    continue
+                # as many waves a SIMD as the LDS allows, up to four, or two
+                for occ in sorted({min(4, LDS_BYTES // lds * waves // 4), 2}):
+                    blocks = min(LDS_BYTES // lds, occ * 4 // waves)
+                    if blocks < 1 or blocks * waves < 8 or blocks * (ns - 1) * st < 24 * 1024:
+                        continue
+                    # at most 16 direct loads of a wave in flight behind the stage waited for
+                    if (ns - 2) * (st // 1024 // waves + 1) > 16:
+                        continue
+                    out.append(stage_config(dt, wm, quads, sym, gauss, rt, ns, kg, occ))
+    return out
+
+
+STAGE_DTYPES = ("r64", "c128", "r32", "c64")
+
+
+def stage_gauss_classes(dt):
+    """(blocks, groups) classes of the complex types that have a kernel in
+    Gauss's three-product form besides the four-product one."""
+    return {"c128": [(4, q) for q in range(9, 17)], "c64": [(4, 16)]}.get(dt, [])
+
+
+def stage_variants(tuned_path=None):
+    """The kernels that stage their rows in LDS: two to four blocks of 16
+    columns of the wider matrix, every count of groups of 4 columns of the
+    narrower one up to as many columns, and the form for a matrix with itself."""
+    tuned = tuned_stage(tuned_path)
+    return [dict(op="tsmttsm", dt=dt, M=0, N=0, maxM=16 * wm, maxN=4 * q,
+                 cfg=tuned.get((dt, wm, q, sym, gauss)) or stage_config(dt, wm, q, sym, gauss))
+            for dt, wm, q, sym, gauss in stage_classes()]
+
+
+def stage_classes():
+    """(dtype, column blocks, groups of four columns, a matrix with itself,
+    three-product form) of every kernel of stage_variants."""
+    out = []
+    for dt in STAGE_DTYPES:
+        for wm in (2, 3, 4):
+            for q in range(1, 4 * wm + 1):
+                out.append((dt, wm, q, False, False))
+                if (wm, q) in stage_gauss_classes(dt):
+                    out.append((dt, wm, q, False, True))
+            out += [(dt, wm, q, True, False) for q in range(4 * wm - 3, 4 * wm + 1)]
+    return out
+
+
+def tuned_stage(path=None):
+    """{class of stage_classes: configuration} chosen by the autotuner
+    (tuned.json key "stage")."""
+    path = path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned.json")
+    out = {}
+    if os.path.exists(path):
+        with open(path) as f:
+            for e in json.load(f).get("stage", []):
+                key = (e["dt"], e["wm"], e["quads"], e["sym"], e["gauss"])
+                how = dict(RT=e["RT"], NS=e["NS"], KG=e["KG"], OCC=e["OCC"])
+                out[key] = stage_config(*key, **how)
+                # odd counts of groups take the choice of the next one
+                odd = key[:2] + (e["quads"] - 1,) + key[3:]
+                out.setdefault(odd, stage_config(*odd, **how))
+    # a matrix with itself: the stages and row groups of two matrices of its
+    # width, so that both are summed in the same order (with a stage more in
+    # flight, as a stage holds half the bytes)
+    for (dt, wm, q, _, gauss), c in list(out.items()):
+        if q > 4 * wm - 4 and (gauss or (wm, q) not in stage_gauss_classes(dt)):
+            out[(dt, wm, q, True, False)] = stage_config(dt, wm, q, True, False, RT=c["RT"], NS=c["NS"] + 1,
+                                                         KG=c["KG"], OCC=c["OCC"])
+    return out
+
+
 def tuning_variants(widths):
     """All candidates of every (op, dtype, width) in ``widths``, plus the
     run-time-width variants (the library the autotuner times)."""
@@ -728,7 +788,7 @@ def load_tuned(path):
 def needs_layout(cfg):
     """True if a configuration reads A in a way only some layouts allow
     (paired loads, slab reads, direct loads of whole stages into LDS)."""
-    return bool(cfg.get("VA") or cfg.get("FL") or cfg.get("kind") in ("lds", "dot"))
+    return bool(cfg.get("VA") or cfg.get("FL") or cfg.get("kind") in ("lds", "dot", "stage"))
 
 
 def exact_variants(widths, tuned=None):
@@ -772,13 +832,17 @@ def variant_name(v):
         tag = "a32_b%dx%dw%d_u%d" % (c["MB"], c["NB"], c["MW"], c["U"])
     elif c["kind"] == "a32":
         tag = "a32_s%dn%d_u%d" % (c["MS"], c["NB"], c["U"])
+    elif c["kind"] == "stage":
+        tag = "lds_%s_k%d_s%d" % ("sym" if c.get("SYM") else "dma", c["RT"], c["NS"])
+        if c["KG"] != 1:
+            tag += "_kg%d" % c["KG"]
     elif c["kind"] == "lds":
         tag = "lds_b%dx%dw%dx%d_k%d" % (c["MB"], c["NB"], c["WM"], c["WN"], c["RT"])
     elif v["op"] == "tsmttsm":
         tag = "mfma_b%dx%dw%d_u%d" % (c["MB"], c["NB"], c["MW"], c["U"])
     else:
         tag = "mfma_s%dn%d_u%d" % (c["MS"], c["NB"], c["U"])
-    if c.get("WPB", WPB) != WPB:
+    if c.get("WPB", WPB) != WPB and c["kind"] != "stage":
         tag += "_w%d" % c["WPB"]
     if c.get("NBUF", 2) != 2:
         tag += "_r%d" % c["NBUF"]
@@ -809,6 +873,10 @@ def _template(v):
     f32 = "true" if is_f32(v["dt"]) else "false"
     if c["kind"] == "packed":
         return "tsg::%s_packed<%d, %d, %d, %s, %d, %d, %s>" % (v["op"], M, N, c["U"], cplx, c["WPB"], nbuf, f32)
+    if c["kind"] == "stage":
+        return "tsg::tsmttsm_stage<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, %d>" % (
+            c["NB"], c["NQ"], c["WM"], c["KG"], c["RT"], c["NS"], cplx, f32, "true" if c.get("G3") else "false",
+            "true" if c.get("SYM") else "false", c["OCC"])
     if c["kind"] == "dot":
         return "tsg::tsmttsm_dot<%d, %d>" % (c["U"], c["WPB"])
     if c["kind"] == "a32" and v["op"] == "tsmttsm":
@@ -820,8 +888,7 @@ def _template(v):
             M, N, c["MS"], c["NB"], c["U"], cplx, c["WPB"], nbuf, c.get("FL", 0), "true" if c.get("RB") else "false",
             "true" if c.get("G3") else "false")
     if c["kind"] == "lds":
-        return "tsg::tsmttsm_lds%s<%d, %d, %d, %d, %d, %d, %d, %s, %s, %d, %d>" % (
-            "_a32" if is_a32(v["dt"]) else "",
+        return "tsg::tsmttsm_lds_a32<%d, %d, %d, %d, %d, %d, %d, %s, %s, %d, %d>" % (
             M, N, c["MB"], c["NB"], c["WM"], c["WN"], c["RT"], cplx, "true" if c.get("G3") else "false",
             c.get("OCC", 1), c.get("IL", 0))
     if v["op"] == "tsmttsm":
@@ -847,7 +914,7 @@ def rows_per_tile(v):
     c = v["cfg"]
     if c["kind"] == "packed":
         return (4 if v["op"] == "tsmttsm" else 16) * c["U"] * c["WPB"]
-    if c["kind"] == "lds":
+    if c["kind"] in ("lds", "stage"):
         return c["RT"]
     if c["kind"] == "dot":
         return 2 * 64 * c["U"] * c["WPB"]
@@ -859,6 +926,14 @@ def rows_per_tile(v):
 def _launcher(v, fn):
     tmpl = _template(v)
     threads = 64 * v["cfg"]["WPB"]
+    if v["cfg"]["kind"] == "stage":
+        # the wider matrix is the kernel's X
+        return ("void %s(const tsg::Launch& p)\n{\n    const bool swap = p.M < p.N;\n"
+                "    hipLaunchKernelGGL((%s), dim3(p.grid), dim3(%d), p.lds, p.stream, p.K, swap ? p.N : p.M,\n"
+                "                       swap ? p.M : p.N, swap ? p.X : p.A, swap ? p.ldx : p.lda, swap ? p.A : p.X,\n"
+                "                       swap ? p.lda : p.ldx, static_cast<double*>(p.Y), p.ldy, p.ws, p.conj, (int)swap);\n}\n"
+                "const void* %s() { return reinterpret_cast<const void*>(&%s); }\n"
+                % (fn, tmpl, threads, fn.replace("launch_", "kernel_"), tmpl))
     if v["op"] == "tsmttsm":
         args = "p.K, p.M, p.N, p.A, p.lda, p.X, p.ldx, static_cast<double*>(p.Y), p.ldy, p.ws, p.conj"
     else:
@@ -882,10 +957,12 @@ def _record(v, fn):
     flat_a = int(bool(c.get("FL")) or c["kind"] in ("lds", "dot"))
     read_b = int(bool(c.get("RB")))
     align16 = int(c["kind"] in ("lds", "dot"))
-    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s},\n'
+    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s, %d, %d, %d, %d},\n'
             % (OPS[v["op"]], DTYPES[v["dt"]][0], v["M"], v["N"], v["maxM"], v["maxN"], pair_a, pair_x, even,
                64 * c["WPB"], rows_per_tile(v), pack, flat_a, read_b, align16, variant_name(v),
-               fn.replace("launch_", "kernel_"), fn))
+               fn.replace("launch_", "kernel_"), fn, 0 if c["kind"] != "stage" else 2 if c.get("SYM") else 1,
+               c.get("NS", 0), int(c["kind"] == "stage" and bool(c.get("G3"))),
+               stage_fold(v["dt"], c) if c["kind"] == "stage" else 0))
 
 
 # batched orthogonalisation: input bytes per slab and queue interleave (0: every
@@ -915,10 +992,14 @@ def emit(outdir, variants, per_file=6, exclude=(), batched=None):
     files = []
     recs = []
     decls = []
-    nfiles = max(1, math.ceil(len(variants) / per_file))
-    for fi in range(nfiles):
-        chunk = variants[fi * per_file:(fi + 1) * per_file]
-        body = ['// generated by codegen.py -- do not edit\n#include "tsg_kernels.hpp"\n'
+    # the kernels that stage their rows in LDS have units of their own (other
+    # compiler flags, see build.STAGE_FLAGS)
+    staged = [v for v in variants if v["cfg"]["kind"] == "stage"]
+    other = [v for v in variants if v["cfg"]["kind"] != "stage"]
+    chunks = [vs[i:i + per_file] for vs in (other, staged) for i in range(0, len(vs), per_file)] or [[]]
+    for fi, chunk in enumerate(chunks):
+        head = "tsg_stage.hpp" if chunk and chunk[0]["cfg"]["kind"] == "stage" else "tsg_kernels.hpp"
+        body = ['// generated by codegen.py -- do not edit\n#include "%s"\n' % head +
                 '#include "tsg_registry.hpp"\n\nnamespace tsg_gen {\n']
         for k, v in enumerate(chunk):
             fn = "launch_%s" % variant_name(v)
@@ -970,7 +1051,7 @@ def all_variants(widths=None, tuned_path=None):
         if (M, N) not in seen:
             seen.add((M, N))
             uniq.append((M, N))
-    return exact_variants(uniq, load_tuned(tuned_path)) + generic_variants(tuned_path)
+    return exact_variants(uniq, load_tuned(tuned_path)) + generic_variants(tuned_path) + stage_variants(tuned_path)
 
 
 def template_of(v):

@@ -24,6 +24,7 @@ struct Launch {
     int64_t ldy;
     double alpha, beta;
     double* ws;  // TSMTTSM: one slot of M*N (x2 complex) doubles per block
+    size_t lds;  // bytes of LDS of a block, for kernels that size it at run time
 };
 
 enum OpKind { OP_TSMTTSM = 0, OP_TSMM = 1 };
@@ -45,7 +46,26 @@ struct Variant {
     const char* name;
     const void* (*kernel)(); // device function, for occupancy queries
     void (*launch)(const Launch&);
+    // TSMTTSM with the rows staged in LDS by direct loads, run-time widths:
+    // 1 for any two matrices, 2 for a matrix with itself; serves the widths
+    // whose 16-column blocks (wider matrix) and 4-column groups (narrower one)
+    // are exactly maxM / 16 and maxN / 4 (0: not such a kernel)
+    int stage;
+    int stages;         // its stages in LDS
+    int gauss;          // it forms complex products from three real ones
+    int fold;           // LDS bytes of its sum over row groups
 };
+
+// LDS bytes of a block of the staged kernel: NS stages of RT rows of both
+// matrices in whole 1 KB pieces (sym: of one matrix), and 1 KB past the last,
+// where the operand reads of columns past a width may reach; at least `fold`
+// bytes, which the sum over row groups takes after the last stage.
+inline size_t stage_lds_bytes(int wide, int narrow, size_t es, int RT, int NS, bool sym, size_t fold)
+{
+    const size_t x = (wide * es * RT + 1023) / 1024, y = sym ? 0 : (narrow * es * RT + 1023) / 1024;
+    const size_t b = (x + y) * 1024 * NS + 1024;
+    return b > fold ? b : fold;
+}
 
 extern const Variant kVariants[];
 extern const int kNumVariants;

@@ -10,11 +10,13 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <utility>
 #include <vector>
 
 #include "../../include/tsgemm.h"
 #include "tsg_registry.hpp"
+
 
 namespace tsg {
 
@@ -149,7 +151,8 @@ std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 // Outgrown workspaces, kept until tsg_finalize: a graph captured earlier on
 // the stream may still hold one of them and write its partial sums there.
 std::vector<std::pair<int, void*>> g_retired;
-std::map<std::pair<int, const tsg::Variant*>, int> g_occ;  // (device, variant) -> blocks per CU
+// (device, variant, LDS bytes of a block) -> blocks per CU
+std::map<std::tuple<int, const tsg::Variant*, size_t>, int> g_occ;
 
 std::map<int, double*> g_scratch;  // device -> device address of its no-alloc scratch
 
@@ -197,14 +200,17 @@ tsg_status current_device(int* dev)
     return TSG_OK;
 }
 
-int occupancy(int dev, const tsg::Variant& v)
+int occupancy(int dev, const tsg::Variant& v, size_t lds)
 {
     std::lock_guard<std::mutex> lk(g_mu);
-    auto key = std::make_pair(dev, &v);
+    auto key = std::make_tuple(dev, &v, lds);
     auto it = g_occ.find(key);
     if (it != g_occ.end()) return it->second;
+    // more than the 64 KB a block may ask for by default
+    if (lds > (64u << 10))
+        hipFuncSetAttribute(v.kernel(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, v.kernel(), v.threads, 0) != hipSuccess || blocks < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, v.kernel(), v.threads, lds) != hipSuccess || blocks < 1)
         blocks = 1;
     g_occ[key] = blocks;
     return blocks;
@@ -250,6 +256,58 @@ const tsg::Variant* pick(int op, tsg_dtype dt, int M, int N, const void* A, int6
     return v;
 }
 
+// The kernel that stages its rows in LDS serves every width above 16 (up to
+// 16 x 16 row packing reads as fast and fills its fragments), of the layouts
+// stage_reads takes; odd real leading dimensions and unaligned matrices stay
+// with the register rings (24 columns of a 64-column basis against 8: 66 us
+// at 2^20 rows by either).
+//
+// Whether it can read a tall matrix of width W: 16-byte chunks of a tile's packed rows, so contiguous rows of any
+// width, or rows that are whole chunks 16-byte aligned (and a tile that spans
+// less than 2^31 bytes, the reach of its 32-bit offsets).
+bool stage_reads(const tsg::Variant& v, size_t es, int W, const void* p, int64_t ld)
+{
+    if (!aligned(p, 16)) return false;
+    if (ld == W) return true;
+    return W * es % 16 == 0 && ld * es % 16 == 0 && ld < (int64_t)((size_t)1 << 31) / (int64_t)(es * v.rows_per_tile);
+}
+
+// Complex widths summed in Gauss's three-product form, whose imaginary part
+// has the larger error bound: squares of 49 .. 64 columns (64 x 64 at 2^22
+// rows: 1.87 ms, four products 2.22 ms) and 49 .. 64 columns of A against 33
+// .. 48 of B (64 x 48: 1.47 and 1.76 ms), which the kernels before this one
+// summed that way too; no other width trades accuracy for it.
+bool stage_gauss(int dt, int M, int N)
+{
+    if (dt == TSG_C64) return M == 64 && N == 64;
+    return dt == TSG_C128 && M > 48 && (M == N || (N > 32 && N <= 48));
+}
+
+bool stage_serves(const tsg::Variant& v, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb)
+{
+    const int wide = M > N ? M : N, narrow = M > N ? N : M;
+    const size_t es = elem_bytes((tsg_dtype)v.dt);
+    if (v.maxM != (wide + 15) / 16 * 16) return false;
+    if (v.maxN != (narrow + 3) / 4 * 4) return false;
+    if (v.stage == 2) return M == N && A == B && lda == ldb && stage_reads(v, es, M, A, lda);
+    return stage_reads(v, es, M, A, lda) && stage_reads(v, es, N, B, ldb);
+}
+
+// The LDS-staged kernel of a TSMTTSM, or null: widths above 16, 16-byte
+// aligned matrices of a layout it can read; a matrix with itself (a Gram
+// matrix) takes the form that reads it once and forms half of the products.
+const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb)
+{
+    if (M <= 16 && N <= 16) return nullptr;
+    const bool sym = M == N && A == B && lda == ldb;
+    const int gauss = !sym && stage_gauss(dt, M, N);
+    for (int i = 0; i < tsg::kNumVariants; ++i) {
+        const tsg::Variant& v = tsg::kVariants[i];
+        if (v.stage == (sym ? 2 : 1) && v.dt == dt && v.gauss == gauss && stage_serves(v, M, N, A, lda, B, ldb)) return &v;
+    }
+    return nullptr;
+}
+
 const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_t lda, const void* X,
                              int64_t ldx, bool beta_nz)
 {
@@ -263,6 +321,7 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
         for (int i = 0; i < tsg::kNumVariants; ++i) {
             const tsg::Variant& v = tsg::kVariants[i];
             if (g_force != v.name) continue;
+            if (v.stage) return v.op == op && v.dt == dt && stage_serves(v, M, N, A, lda, X, ldx) ? &v : nullptr;
             const bool serves = (v.M == M && v.N == N) || (v.M == 0 && M <= v.maxM && N <= v.maxN);
             if (v.op == op && v.dt == dt && serves && (!v.pairA || a_pairs) && (!v.pairX || x_pairs) &&
                 (!v.flatA || rows_contiguous) && (!v.readB || beta_nz) && (!v.align16 || ax16))
@@ -270,9 +329,11 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
         }
         return nullptr;
     }
+    if (op == tsg::OP_TSMTTSM)
+        if (const tsg::Variant* v = pick_stage(dt, M, N, A, lda, X, ldx)) return v;
     for (int i = 0; i < tsg::kNumVariants; ++i) {
         const tsg::Variant& v = tsg::kVariants[i];
-        if (v.op != op || v.dt != dt) continue;
+        if (v.op != op || v.dt != dt || v.stage) continue;
         if (v.pairA && !a_pairs) continue;
         if (v.pairX && !x_pairs) continue;
         if (v.flatA && !rows_contiguous) continue;
@@ -345,13 +406,33 @@ tsg_status validate(tsg_dtype dt, int64_t K, int32_t M, int32_t N, const void* A
     return TSG_OK;
 }
 
+// LDS bytes of a block that the launch asks for (kernels with run-time sizes).
+size_t lds_for(const tsg::Variant& v, int M, int N)
+{
+    if (!v.stage) return 0;
+    const size_t es = elem_bytes((tsg_dtype)v.dt);
+    const int wide = M > N ? M : N, narrow = M > N ? N : M;
+    return tsg::stage_lds_bytes(wide, narrow, es, v.rows_per_tile, v.stages, v.stage == 2, v.fold);
+}
+
 int grid_for(int dev, const tsg::Variant& v, int64_t K, int M, int N, int cus)
 {
+    if (v.stage == 2) {
+        // a matrix with itself: the grid of two matrices of its width, whose
+        // kernel has the same stages and row groups, so that A^T A is summed
+        // in the order of A^T B (that kernel needs more registers and LDS)
+        const int gauss = stage_gauss(v.dt, M, N);
+        for (int i = 0; i < tsg::kNumVariants; ++i) {
+            const tsg::Variant& w = tsg::kVariants[i];
+            if (w.stage == 1 && w.dt == v.dt && w.gauss == gauss && w.maxM == v.maxM && w.maxN == v.maxN)
+                return grid_for(dev, w, K, M, N, cus);
+        }
+    }
     int64_t rows = v.rows_per_tile;
     if (v.pack == 1) rows *= 16 / (M > N ? M : N);
     if (v.pack == 2) rows *= 16 / N;
     const int64_t tiles = (K + rows - 1) / rows;
-    const int64_t cap = (int64_t)cus * occupancy(dev, v);
+    const int64_t cap = (int64_t)cus * occupancy(dev, v, lds_for(v, M, N));
     int64_t g = tiles < cap ? tiles : cap;
     if (v.op == tsg::OP_TSMTTSM) {
         // the per-block partial sums of a launch always fit the no-alloc
@@ -427,6 +508,7 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
         if ((s = get_workspace(dev, p.stream, need, &w)) != TSG_OK) return s;
         p.ws = static_cast<double*>(w->data);
     }
+    p.lds = lds_for(*v, M, N);
     v->launch(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));
@@ -525,9 +607,17 @@ size_t tsg_workspace_size(int32_t op_kind, tsg_dtype dt, int64_t K, int32_t M, i
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     DeviceInfo di;
     if (device_info(dev, &di) != TSG_OK) return 0;
-    const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, nullptr, M + (M & 1), nullptr, N + (N & 1));
-    if (!v) return 0;
-    return tsmttsm_ws_bytes(grid_for(dev, *v, K, M, N, di.cus), M, N, is_complex(dt));
+    // the larger need of contiguous and of padded rows (aligned matrices; one
+    // with itself runs the grid of two)
+    alignas(16) static const char buf16[32] = {0};
+    size_t need = 0;
+    for (int pad = 0; pad < 2; ++pad) {
+        const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, buf16, M + pad * (M & 1), buf16 + 16, N + pad * (N & 1));
+        if (!v) continue;
+        const size_t b = tsmttsm_ws_bytes(grid_for(dev, *v, K, M, N, di.cus), M, N, is_complex(dt));
+        need = need > b ? need : b;
+    }
+    return need;
 }
 
 tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stream)
@@ -545,7 +635,10 @@ tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stre
     for (int i = 0; i < tsg::kNumVariants; ++i) {
         const tsg::Variant& v = tsg::kVariants[i];
         if (v.op != tsg::OP_TSMTTSM || v.dt != (int)dt) continue;
-        if (!((v.M == M && v.N == N) || (v.M == 0 && M <= v.maxM && N <= v.maxN))) continue;
+        if (v.stage) {
+            const int wide = M > N ? M : N, narrow = M > N ? N : M;
+            if (v.maxM != (wide + 15) / 16 * 16 || v.maxN != (narrow + 3) / 4 * 4 || (v.stage == 2 && M != N)) continue;
+        } else if (!((v.M == M && v.N == N) || (v.M == 0 && M <= v.maxM && N <= v.maxN))) continue;
         size_t b = tsmttsm_ws_bytes(grid_for(dev, v, K, M, N, di.cus), M, N, is_complex(dt));
         if (b > need) need = b;
     }
@@ -648,10 +741,9 @@ const char* tsg_kernel_name(int32_t op_kind, tsg_dtype dt, int32_t conj, int32_t
     (void)conj;
     if (op_kind != 0 && op_kind != 1) return "";
     if (M < 1 || N < 1 || M > kMaxWidth || N > kMaxWidth) return "";
-    alignas(16) static const char buf16[16] = {0};
-    const void* al = static_cast<const void*>(buf16);
-    // contiguous rows (lda = M, ldb = N), 16-byte aligned operands
-    const tsg::Variant* v = pick(op_kind, dt, M, N, al, M, al, N);
+    alignas(16) static const char buf16[32] = {0};
+    // contiguous rows (lda = M, ldb = N), two 16-byte aligned operands
+    const tsg::Variant* v = pick(op_kind, dt, M, N, buf16, M, buf16 + 16, N);
     return v ? v->name : "";
 }
 

@@ -60,6 +60,11 @@ def cmd_build(args):
     sys.path.insert(0, ROOT)
     from paper_1905_03136_amd import build, codegen
     lib = TUNE_LIB if not args.tag else build.tagged_lib(args.tag)
+    if args.stage:
+        # the candidates of the kernels that stage their rows in LDS
+        build.build(variants=[v for _, v in stage_tuning_variants()] + codegen.generic_variants(), lib_path=lib,
+                    tag="_" + (args.tag or "tune"))
+        return
     if args.generic:
         # the run-time-width classes' candidates (plus the product's own
         # run-time-width variants, so that every pair has a kernel)
@@ -283,6 +288,56 @@ def cmd_run(args):
     db.close()
     print("[tune] done in %.0f s" % (time.time() - t_start), flush=True)
     write_table(args.db, args.out, args.merge)
+
+
+def stage_tuning_variants():
+    """[(class, variant)] of every candidate of the kernels that stage their
+    rows in LDS (codegen.stage_classes with an even count of groups: an odd
+    count takes the choice of the next, and a matrix with itself that of two
+    matrices)."""
+    from paper_1905_03136_amd import codegen
+    return [(cls, dict(op="tsmttsm", dt=cls[0], M=0, N=0, maxM=16 * cls[1], maxN=4 * cls[2], cfg=c))
+            for cls in codegen.stage_classes() if cls[2] % 2 == 0 and not cls[3]
+            for c in codegen.stage_candidates(*cls)]
+
+
+def cmd_stage(args):
+    """GPU: time the candidates of every class of the kernels that stage their
+    rows in LDS on two width pairs of the class (its largest widths, and odd
+    ones with the wider matrix second) and write the choice of each (the
+    fastest by the mean over the pairs of time over the pair's best) into the
+    table's "stage" list."""
+    sys.path.insert(0, ROOT)
+    from paper_1905_03136_amd import build, codegen
+    os.environ.setdefault("TSG_LIBRARY", build.tagged_lib(args.tag))
+    timer = _Timer(args.K, args.warmup, args.reps)
+    groups = {}
+    for cls, v in stage_tuning_variants():
+        groups.setdefault(cls, []).append(v)
+    entries = []
+    for cls, vs in groups.items():
+        dt, wm, q, sym, gauss = cls
+        pairs = [(16 * wm, 4 * q), (4 * q - 1, 16 * wm - (5 if q < 4 * wm else 0))]
+        by = {}
+        for M, N in pairs:
+            recs = [r for r in timer.measure("tsmttsm", dt, M, N, vs) if r.get("us")]
+            assert all(r["ok"] for r in recs), [r["name"] for r in recs if not r["ok"]]
+            best = min(r["us"] for r in recs)
+            for r in recs:
+                by.setdefault(r["name"], []).append((r["us"] / best, r))
+        name = min(by, key=lambda n: sum(x for x, _ in by[n]))
+        c = by[name][0][1]["cfg"]
+        entries.append(dict(dt=dt, wm=wm, quads=q, sym=sym, gauss=gauss, RT=c["RT"], NS=c["NS"], KG=c["KG"],
+                            OCC=c["OCC"], name=name, pairs=[[r["M"], r["N"], r["us"], r["GBps"]] for _, r in by[name]]))
+        print("[tune] %-55s %s" % (name, entries[-1]["pairs"]), flush=True)
+    tab = {"entries": []}
+    if os.path.exists(args.out):
+        with open(args.out) as f:
+            tab = json.load(f)
+    tab["stage"] = entries
+    with open(args.out, "w") as f:
+        json.dump(tab, f, indent=1)
+        f.write("\n")
 
 
 def generic_tuning_variants():
@@ -652,6 +707,7 @@ def main(argv=None):
     b.add_argument("--with-tuned", action="store_true", help="add each width's configuration in tuned.json")
     b.add_argument("--tag", default="", help="build _build/libtsgemm_<tag>.so apart from the default tuning library")
     b.add_argument("--generic", action="store_true", help="the candidates of the run-time-width classes")
+    b.add_argument("--stage", action="store_true", help="the candidates of the kernels that stage rows in LDS")
     r = sub.add_parser("run")
     r.add_argument("--widths", default="graded")
     r.add_argument("--dtypes", default="", help="comma-separated subset of r64,c128,r32,c64,r32a,c64a")
@@ -692,6 +748,12 @@ def main(argv=None):
     g.add_argument("--warmup", type=int, default=2)
     g.add_argument("--verbose", action="store_true", help="print every timing")
     g.add_argument("--table-only", action="store_true", help="only write the table from the database")
+    sg = sub.add_parser("stage", help="GPU: configurations of the kernels that stage their rows in LDS")
+    sg.add_argument("--K", type=int, default=1 << 22)
+    sg.add_argument("--tag", default="stage", help="library built by 'build --stage --tag <tag>'")
+    sg.add_argument("--out", default=os.path.join(HERE, "tuned.json"))
+    sg.add_argument("--reps", type=int, default=7)
+    sg.add_argument("--warmup", type=int, default=2)
     t = sub.add_parser("table")
     t.add_argument("--db", default="tune_db.jsonl")
     t.add_argument("--out", default=os.path.join(HERE, "tuned.json"))
@@ -707,6 +769,8 @@ def main(argv=None):
         cmd_batched(a)
     elif a.cmd == "heatmap":
         cmd_heatmap(a)
+    elif a.cmd == "stage":
+        cmd_stage(a)
     elif a.cmd == "generic":
         if a.table_only:
             write_generic(a.db, a.out)
