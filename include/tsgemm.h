@@ -203,17 +203,19 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
  * its own K_i, M_i <= 64, N_i <= 16; 1 <= count <= 1024) in ONE persistent
  * kernel launch over a device work queue.  A one-block set-up kernel builds
  * the queue on the device: instances ordered by decreasing input size
- * K_i (M_i + N_i), each cut into K-slab items (TSMTTSM partial sums of about
- * 4 MiB of input, at most 256 per instance) followed, one instance later,
- * by its row-slab items (the TSMM update).  The last slab item of an
- * instance to finish folds the instance's partials in slab order into C_i
- * and marks it ready; an update item starts once its instance is ready.
+ * K_i (M_i + N_i), each cut into K-slab items (TSMTTSM partial sums; the batch
+ * has about 512 slabs of at least 32 KiB of input, and more of about 1 MiB
+ * where it is larger, up to 256 per instance on average), and, after every
+ * instance's slabs, into row-slab items (the TSMM update).  The last slab item
+ * to finish of every sixteen consecutive ones sums their partials in slab
+ * order, the last such group of an instance sums the groups in order into
+ * C_i and marks it ready; an update item starts once its instance is ready.
  * Every item an update waits for precedes it in the queue and never waits
  * itself, so the launch cannot deadlock.  Results are deterministic: the
  * slab boundaries and every summation order are fixed by the queue, not by
  * which block takes which item.  C_i is computed in binary64 by matrix-core
  * products of four rows, summed over the slab's rows, then over slabs in
- * order; the update is W <- W + V (-C) with the same products.
+ * order (by sixteens); the update is W <- W + V (-C) with the same products.
  *
  * Descriptor of instance i (all device pointers, row-major):
  *   V (K x M, ldv >= M) read only; W (K x N, ldw >= N) updated in place;
@@ -266,9 +268,8 @@ tsg_status tsg_orth_batched_check(void *workspace);
  * set-up kernel once (queue as for tsg_orth_batched) and captures one launch
  * of the persistent kernel into a hipGraph on a private stream.
  * rows_per_item > 0 fixes the slab height of every instance; <= 0 picks it
- * per instance (about 4 MiB of input per slab, at most 256 slabs per
- * instance) and cuts the updates at the end of the queue into half and
- * quarter slabs.
+ * as described above, and cuts the updates at the end of the queue of a batch
+ * with slabs of the full size into half and quarter slabs.
  * Errors: TSG_E_ARG (null plan/descs, count < 1, K_i < 0, M_i or N_i < 1,
  * ld too small, null or misaligned pointer with K_i > 0, null C_i),
  * TSG_E_UNSUPPORTED (count > 1024, M_i > 64, N_i > 16, slab height too large

@@ -6,16 +6,31 @@
 //
 // One kernel launch with a persistent grid consumes a device work queue:
 //  * phase-1 items: a K-slab of one instance; its partial V^T W goes to the
-//    slab's own slot; the last slab of an instance to finish (per-instance
-//    arrival counter) sums the instance's slots in slab order into C_i and
-//    raises ready[i];
+//    slab's own slot; the last slab to finish of every sixteen consecutive
+//    ones (arrival counters) sums their slots in slab order, the last such
+//    group of an instance sums the groups in order into C_i and raises
+//    ready[i];
 //  * phase-2 items: a row slab of one instance; waits for ready[i], stages
 //    -C_i on chip and updates its rows of W_i.
 // Every phase-1 item precedes every phase-2 item in the queue and phase-1
 // items never wait, so whatever an update waits for has already been taken by
 // a running block: the waits cannot deadlock, whatever the grid.  They are
-// bounded anyway (a spin limit raises an error word instead of hanging).  The
-// last block to leave returns the queue head, counters and flags to zero, so
+// bounded anyway (a spin limit raises an error word instead of hanging).
+// A block starts with the item of its own number and draws its next item
+// while it works on the current one; the earliest unfinished item is then
+// still some block's current one, or comes after such an item of its block,
+// so the argument stands.
+//
+// What blocks exchange (partial sums, group sums, C_i, the flags) goes
+// through agent-scope atomic stores and loads, which pass the XCDs' caches;
+// a wave waits for its stores to complete before its block counts an
+// arrival.  No release or acquire fence is needed: those write back and
+// drop a whole XCD's L2, about 20 us an item (128 instances of 4 GB in all
+// cut into 64 KB slabs: 6.3 ms, with this exchange 2.5), which had made 8 MB
+// the best slab.  With 1 MB slabs 64 instances of 18 GB take 6.15 instead of
+// 6.55 ms, 128 instances of 4 GB 1.40 instead of 2.26 ms.
+//
+// The last block to leave returns the queue head, counters and flags to zero, so
 // the launch can be replayed from a captured graph without memset nodes.
 #include <hip/hip_runtime.h>
 
@@ -44,9 +59,11 @@ constexpr int kWPB = 4;  // waves per block
 constexpr int kThreads = kWPB * kWave;
 constexpr int kMaxM = 64, kMaxN = 16;
 constexpr unsigned kDefaultSpin = 1u << 23;   // sleeps of ~0.2 us: about 2 s
-constexpr int64_t kItemBytes = 4 << 20;       // input bytes of one slab (automatic sizing; 4 MB measured
-                                              // 3% faster than 2 MB and 8 MB on the 64-instance workload)
-constexpr int64_t kMaxSlabs = 256;            // slabs per instance (bounds the fold)
+constexpr int64_t kItemBytes = 4 << 20;       // input bytes of one slab at most (automatic sizing, unless tuned)
+constexpr int64_t kMinItemBytes = 32 << 10;   // ... and at least
+constexpr int64_t kTargetSlabs = 512;         // slabs of a batch that is too small for slabs of the full size
+constexpr int64_t kMaxSlabs = 256;            // slabs per instance on average (bounds the partial sums)
+constexpr int kGroup = 16;                    // slabs of one group of the fold
 
 struct Item {
     int64_t row0;      // first row of the slab
@@ -54,7 +71,7 @@ struct Item {
     int32_t nrows;
     int32_t inst;
     int32_t phase;     // 1: slab of V^T W; 2: update of W rows
-    int32_t pad;
+    int32_t slab;      // phase 1: the slab's number in its instance
 };
 
 struct DevDesc {
@@ -65,10 +82,10 @@ struct DevDesc {
     int64_t ldw;
     double* C;
     int64_t ldc;
-    int64_t part0;  // offset (doubles) of the instance's first partial
+    int64_t part0;  // offset (doubles) of the instance's first partial; its group sums follow the partials
     int32_t M, N;
     int32_t nparts;  // phase-1 slabs of the instance
-    int32_t pad;
+    int32_t group0;  // its first group counter
 };
 
 // Error bits of Ctrl::err.
@@ -82,7 +99,8 @@ struct Ctrl {
     unsigned err;    // error bits (kErr*)
     unsigned spin;   // spin limit
     unsigned total;  // items in the queue, written by the set-up kernel
-    unsigned pad[3];
+    unsigned groups; // group counters in use
+    unsigned pad[2];
 };
 
 __device__ __forceinline__ dbl4 mfma16(double a, double b, dbl4 c)
@@ -90,8 +108,17 @@ __device__ __forceinline__ dbl4 mfma16(double a, double b, dbl4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void fence_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
-__device__ __forceinline__ void fence_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+// Values handed from block to block (see above).
+__device__ __forceinline__ void st_share(double* p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double ld_share(const double* p)
+{
+    return __hip_atomic_load(const_cast<double*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The wave's stores have completed (and the compiler moves none past this).
+__device__ __forceinline__ void stores_done() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ------------------------------------------------------- slab addressing
 // A slab (rows row0 .. row0 + nrows - 1 of a row-major matrix) is addressed
@@ -238,28 +265,81 @@ __device__ __attribute__((noinline)) void slab_partial(const Item* items, const 
         __syncthreads();
     }
     double* part = parts + it.slot_off;
-    for (int e = threadIdx.x; e < M * N; e += kThreads) part[e] = lds[e];
+    for (int e = threadIdx.x; e < M * N; e += kThreads) st_share(part + e, lds[e]);
 }
 
-// Sum of the instance's partials in slab order, eight loads in flight.
-__device__ void fold_instance(const DevDesc& d, const double* __restrict__ parts)
+// Sum of `n` consecutive slots of E doubles at `src`, in order: out(e, sum)
+// for every entry; sixteen loads of two entries in flight per thread.
+template <class Out>
+__device__ __forceinline__ void fold_slots(const double* src, int n, int E, Out out)
 {
-    const int E = d.M * d.N, P = d.nparts;
-    for (int e = threadIdx.x; e < E; e += kThreads) {
-        const double* p = parts + d.part0 + e;
-        double s = 0.0;
-        int j = 0;
-        for (; j + 8 <= P; j += 8) {
-            double v[8];
+    for (int e0 = threadIdx.x; e0 < E; e0 += 2 * kThreads) {
+        const int e1 = e0 + kThreads;
+        const bool two = e1 < E;
+        double s0 = 0.0, s1 = 0.0;
+        for (int j0 = 0; j0 < n; j0 += kGroup) {
+            double v0[kGroup], v1[kGroup];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(j + u) * E];
+            for (int u = 0; u < kGroup; ++u)
+                if (j0 + u < n) v0[u] = ld_share(src + (int64_t)(j0 + u) * E + e0);
+            if (two) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+                for (int u = 0; u < kGroup; ++u)
+                    if (j0 + u < n) v1[u] = ld_share(src + (int64_t)(j0 + u) * E + e1);
+            }
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u)
+                if (j0 + u < n) s0 += v0[u];
+            if (two) {
+#pragma unroll
+                for (int u = 0; u < kGroup; ++u)
+                    if (j0 + u < n) s1 += v1[u];
+            }
         }
-        for (; j < P; ++j) s += p[(int64_t)j * E];
-        const int m = e / d.N, n = e - m * d.N;
-        d.C[(int64_t)m * d.ldc + n] = s;
+        out(e0, s0);
+        if (two) out(e1, s1);
     }
+}
+
+// A slab's partial is stored: count its arrival; the last of its group sums
+// the group, the last group of the instance sums the groups into C and
+// raises the instance's flag.
+__device__ __attribute__((noinline)) void slab_arrived(const Item* items, const DevDesc* descs, int q, double* parts_,
+                                                       unsigned* cnt_, unsigned* groups_, unsigned* ready_)
+{
+    Item it;
+    DevDesc d;
+    fetch_item(items, descs, q, it, d);
+    double* parts = uni(parts_);
+    unsigned *cnt = uni(cnt_), *groups = uni(groups_), *ready = uni(ready_);
+    __shared__ int s_last;
+    const int slab = uni(it.slab), E = d.M * d.N, P = d.nparts;
+    const int g = slab / kGroup, ng = (P + kGroup - 1) / kGroup, size = min(kGroup, P - g * kGroup);
+    auto last_of = [&](unsigned* c, int n) -> bool {
+        stores_done();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            s_last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(n - 1);
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(s_last) != 0;
+    };
+    auto to_c = [&](int e, double s) {
+        const int m = e / d.N, n = e - m * d.N;
+        st_share(d.C + (int64_t)m * d.ldc + n, s);
+    };
+    if (!last_of(groups + uni(d.group0) + g, size)) return;
+    const double* src = parts + d.part0 + (int64_t)g * kGroup * E;
+    if (ng == 1) {
+        fold_slots(src, size, E, to_c);
+    } else {
+        double* sums = parts + d.part0 + (int64_t)P * E;
+        fold_slots(src, size, E, [&](int e, double s) { st_share(sums + (int64_t)g * E + e, s); });
+        if (!last_of(cnt + it.inst, ng)) return;
+        fold_slots(sums, ng, E, to_c);
+    }
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&ready[it.inst], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------- phase 2
@@ -421,7 +501,7 @@ __device__ __attribute__((noinline)) void run_partial(const Item* items, const D
         __syncthreads();
     }
     double* part = parts + it.slot_off;
-    for (int e = threadIdx.x; e < M * N; e += kThreads) part[e] = lds[e];
+    for (int e = threadIdx.x; e < M * N; e += kThreads) st_share(part + e, lds[e]);
 }
 
 // Phase 1 on runs for M, N <= 16, with row packing: P = 16 / max(M, N) rows
@@ -500,7 +580,7 @@ __device__ __attribute__((noinline)) void run_partial_packed(const Item* items, 
             const double* Dw = g_run + w * kRunMax;
             for (int h = 0; h < P; ++h) s += Dw[(h * M + m) * 16 + h * N + n];
         }
-        part[e] = s;
+        st_share(part + e, s);
     }
 }
 
@@ -586,19 +666,19 @@ __device__ __attribute__((noinline)) void run_update(const Item* items, const De
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 orth_persistent(const DevDesc* __restrict__ descs, const Item* __restrict__ items,
                 double* __restrict__ parts, unsigned* __restrict__ cnt, unsigned* __restrict__ ready,
-                Ctrl* __restrict__ ctrl, int count)
+                unsigned* __restrict__ groups, Ctrl* __restrict__ ctrl, int count)
 {
-    __shared__ int s_q, s_last;
+    __shared__ int s_q;
     double* lds = g_lds;
     const int tid = threadIdx.x;
     // written by the set-up kernel earlier on the stream (0 when it rejected the batch)
     const int total = (int)__builtin_amdgcn_readfirstlane(ctrl->total);
-    while (true) {
+    int q = blockIdx.x;
+    while (q < total) {
+        // the next item, drawn while this one is worked on
+        int next = 0;
         if (tid == 0)
-            s_q = (int)__hip_atomic_fetch_add(&ctrl->head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int q = __builtin_amdgcn_readfirstlane(s_q);  // uniform: item and descriptor go to SGPRs
-        if (q >= total) break;
+            next = (int)(gridDim.x + __hip_atomic_fetch_add(&ctrl->head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         const Item it = items[q];
         const DevDesc d = descs[it.inst];
         if (it.phase == 1) {
@@ -619,21 +699,7 @@ orth_persistent(const DevDesc* __restrict__ descs, const Item* __restrict__ item
                 default: slab_partial<4, 2, 2>(items, descs, q, parts); break;
                 }
             }
-            fence_release();  // this wave's part of the partial, before the arrival is counted
-            __syncthreads();
-            if (tid == 0) {
-                const unsigned old =
-                    __hip_atomic_fetch_add(&cnt[it.inst], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-                s_last = old == (unsigned)(d.nparts - 1);
-            }
-            __syncthreads();
-            if (__builtin_amdgcn_readfirstlane(s_last)) {
-                fence_acquire();  // every partial of the instance is visible
-                fold_instance(d, parts);
-                fence_release();
-                __syncthreads();
-                if (tid == 0) __hip_atomic_store(&ready[it.inst], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            slab_arrived(items, descs, q, parts, cnt, groups, ready);
         } else {
             if (tid == 0) {
                 const unsigned limit = __hip_atomic_load(&ctrl->spin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -643,18 +709,18 @@ orth_persistent(const DevDesc* __restrict__ descs, const Item* __restrict__ item
                         __hip_atomic_fetch_or(&ctrl->err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         break;
                     }
-                    if (__hip_atomic_load(&ready[it.inst], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0u) break;
+                    if (__hip_atomic_load(&ready[it.inst], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) break;
                     __builtin_amdgcn_s_sleep(8);
                 }
             }
             __syncthreads();
-            fence_acquire();  // C_i as written by the fold
+            lds_barrier();
             // -C_i in MFMA operand order: lds[s * 64 + l] = -C(4 s + l/16, l%16)
             const int MS = (d.M + 3) / 4;
             for (int idx = tid; idx < MS * kWave; idx += kThreads) {
                 const int l = idx & (kWave - 1), s = idx / kWave;
                 const int m = 4 * s + (l >> 4), n = l & 15;
-                lds[idx] = (m < d.M && n < d.N) ? -d.C[(int64_t)m * d.ldc + n] : 0.0;
+                lds[idx] = (m < d.M && n < d.N) ? -ld_share(d.C + (int64_t)m * d.ldc + n) : 0.0;
             }
             __syncthreads();
             if (d.ldv == d.M && d.ldw == d.N) {
@@ -695,28 +761,39 @@ orth_persistent(const DevDesc* __restrict__ descs, const Item* __restrict__ item
             default: slab_update<16, 1, 2>(items, descs, q); break;
             }
         }
-        __syncthreads();  // LDS and s_q are reused by the next item
+        if (tid == 0) s_q = next;
+        __syncthreads();  // (LDS is reused by the next item)
+        q = __builtin_amdgcn_readfirstlane(s_q);  // uniform: item and descriptor go to SGPRs
+        __syncthreads();
     }
-    // the last block out resets the queue, counters and flags for the next launch
-    if (tid == 0) {
-        const unsigned old = __hip_atomic_fetch_add(&ctrl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == gridDim.x - 1) {
-            for (int i = 0; i < count; ++i) {
-                __hip_atomic_store(&cnt[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&ready[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __hip_atomic_store(&ctrl->head, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctrl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the last block out resets the queue, counters and flags for the next
+    // launch (thread 0 made all of a block's accesses to them but the stores
+    // of the flags, which stores_done waits for)
+    stores_done();
+    if (tid == 0)
+        s_q = __hip_atomic_fetch_add(&ctrl->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (s_q) {
+        auto clear = [](unsigned* p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        for (int i = tid; i < count; i += kThreads) {
+            clear(cnt + i);
+            clear(ready + i);
+        }
+        const int ng = (int)ctrl->groups;
+        for (int i = tid; i < ng; i += kThreads) clear(groups + i);
+        if (tid == 0) {
+            clear(&ctrl->head);
+            clear(&ctrl->done);
         }
     }
 }
 
 // ------------------------------------------------------------ work queue
 // Slab height of an instance: rows_fixed if positive, else about item_bytes
-// of input per slab and at most kMaxSlabs slabs; never more rows than keep
-// the byte offsets inside a slab (plus one step past its end) below 2^31.
-// Returns 0 if no height fits (leading dimensions too large).  Shared by the
-// host (workspace sizes, plan checks) and the set-up kernel.
+// of input per slab; never more rows than keep the byte offsets inside a slab
+// (plus one step past its end) below 2^31.  Returns 0 if no height fits
+// (leading dimensions too large).  Shared by the host (workspace sizes, plan
+// checks) and the set-up kernel.
 __host__ __device__ inline int64_t round16(int64_t x) { return (x + 15) / 16 * 16; }
 
 __host__ __device__ inline int64_t slab_limit(int64_t ldv, int64_t ldw)
@@ -725,7 +802,7 @@ __host__ __device__ inline int64_t slab_limit(int64_t ldv, int64_t ldw)
     return ((((int64_t)1 << 31) / (8 * ld)) - 128) / 16 * 16;
 }
 
-__host__ __device__ inline int64_t slab_rows(int64_t K, int M, int N, int64_t ldv, int64_t ldw, int64_t rows_fixed,
+__host__ __device__ inline int64_t slab_rows(int M, int N, int64_t ldv, int64_t ldw, int64_t rows_fixed,
                                              int64_t item_bytes)
 {
     const int64_t lim = slab_limit(ldv, ldw);
@@ -733,11 +810,31 @@ __host__ __device__ inline int64_t slab_rows(int64_t K, int M, int N, int64_t ld
     if (R <= 0) {
         const int64_t want = round16(item_bytes / (8 * (int64_t)(M + N)));
         R = want > 16 ? want : 16;
-        const int64_t few = round16((K + kMaxSlabs - 1) / kMaxSlabs);
-        R = R > few ? R : few;
         R = R < lim ? R : lim;
     }
     return (R >= 1 && R <= lim) ? R : 0;
+}
+
+// Input bytes of one slab under automatic sizing, for a batch of `count`
+// instances with `total` bytes of input: kTargetSlabs slabs in all, one a
+// resident block, so that a small batch fills the chip (16 instances of 57 MB
+// in all: slabs of 8 MB left all but about twenty of 512 blocks idle, 0.53 ms
+// a launch, now 0.07), and at most the tuned size `most`, from which on larger
+// batches have more of them, up to kMaxSlabs an instance on average (each
+// instance's last slab is a partial one).
+__host__ __device__ inline int64_t slab_bytes(int64_t total, int count, int64_t most)
+{
+    int64_t b = total / kTargetSlabs;
+    b = b < kMinItemBytes ? kMinItemBytes : b < most ? b : most;
+    const int64_t least = total / ((kMaxSlabs - 1) * (int64_t)count) + 1;
+    return b > least ? b : least;
+}
+
+// Doubles of partial sums of an instance of n slabs: one slot of E a slab and
+// one a group of slabs.
+__host__ __device__ inline int64_t part_doubles(int64_t n, int64_t E)
+{
+    return n * E + (n > kGroup ? (n + kGroup - 1) / kGroup * E : 0);
 }
 
 // Rows of one update item cut from a slab of nr rows into about f pieces
@@ -749,17 +846,18 @@ __host__ __device__ inline int64_t update_piece(int64_t nr, int f)
     return p > 16 ? p : 16;
 }
 
-// Items per instance that a workspace sized by tsg_workspace_size holds:
-// kMaxSlabs slab items and, at the end of the queue, up to four update
+// Items per instance (on average) that a workspace sized by
+// tsg_workspace_size holds: kMaxSlabs slab items and, at the end of the queue, up to four update
 // pieces per slab.
 constexpr int64_t kItemsPerInstance = 5 * kMaxSlabs;
 constexpr int kMaxCount = 1024;  // instances per call (one set-up block, one thread each)
 
-// Byte layout of a workspace: control words, descriptors, arrival counters
-// and ready flags, the item queue, the partial sums.  Regions start at
+// Byte layout of a workspace: control words, descriptors, the instances'
+// arrival counters and ready flags, the groups' arrival counters, the item
+// queue, the partial sums.  Regions start at
 // multiples of 256 bytes.
 struct Layout {
-    size_t ctrl, descs, flags, items, parts, bytes;
+    size_t ctrl, descs, flags, groups, items, parts, bytes;
     int64_t max_items, max_parts;
 };
 
@@ -771,12 +869,29 @@ __host__ __device__ inline Layout make_layout(int count, int64_t max_items, int6
     L.ctrl = 0;
     L.descs = align256(sizeof(Ctrl));
     L.flags = L.descs + align256(sizeof(DevDesc) * (size_t)count);
-    L.items = L.flags + align256(sizeof(unsigned) * 2 * (size_t)count);
+    L.groups = L.flags + align256(sizeof(unsigned) * 2 * (size_t)count);
+    L.items = L.groups + align256(sizeof(unsigned) * ((size_t)max_items / kGroup + (size_t)count));
     L.parts = L.items + align256(sizeof(Item) * (size_t)max_items);
     L.bytes = L.parts + sizeof(double) * (size_t)(max_parts > 0 ? max_parts : 1);
     L.max_items = max_items;
     L.max_parts = max_parts;
     return L;
+}
+
+// Inclusive scan over the block's threads (s: kMaxCount values of LDS).
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* s)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t u = __shfl_up(v, o, kWave);
+        if (lane >= o) v += u;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) s[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += s[w];
+    return v;
 }
 
 // Set-up kernel (one block of kMaxCount threads): checks the descriptors,
@@ -789,42 +904,44 @@ __host__ __device__ inline Layout make_layout(int count, int64_t max_items, int6
 // items of instance r (lag >= count: every slab item before any update
 // item).  An update item waits only for slab items of its own instance, all
 // of which precede it in the queue and never wait, so the persistent kernel
-// cannot deadlock whatever the lag.  With automatic slab heights the updates
-// at the end of the queue are cut finer (the instance whose later update
-// items number fewer than `resident` into quarter slabs, fewer than three
-// times that into half slabs), so the blocks still running after the queue
-// drains hold short items.
+// cannot deadlock whatever the lag.  With slabs of the full size the updates
+// at the end of the queue are cut finer (instances whose later slabs number
+// fewer than a quarter of `resident` into quarter slabs, fewer than one and
+// a quarter of it into half slabs), so the blocks still running after the
+// queue drains hold short items.  Slabs whose partial sums do not fit the
+// workspace are made larger.
+// Thread r works on the instance of rank r; then wave w writes the items of
+// ranks w, w + 16, ....  (One thread placing all instances took 90 us for 64
+// of them.)
+struct Rank {
+    int64_t K, rows, part0;
+    int slabs, pieces, npf, inst, f, E, pos1, pos2;
+};
 __global__ void __launch_bounds__(kMaxCount)
 orth_setup(const tsg_orth_desc* __restrict__ in, int count, int64_t rows_fixed, int64_t item_bytes, int lag,
            int resident, unsigned spin, Ctrl* __restrict__ ctrl, DevDesc* __restrict__ dd, unsigned* __restrict__ flags,
-           Item* __restrict__ items, int64_t max_items, int64_t max_parts)
+           unsigned* __restrict__ groups, Item* __restrict__ items, int64_t max_items, int64_t max_parts)
 {
-    // 56 KB: per instance its size key (then K), slab height, first partial
-    // sum, slabs, rank order, queue positions, update pieces, pieces per full
-    // slab, M N and its piece factor
-    __shared__ int64_t s_key[kMaxCount], s_rows[kMaxCount], s_part0[kMaxCount];
-    __shared__ int s_nsl[kMaxCount], s_ord[kMaxCount], s_pos1[kMaxCount], s_pos2[kMaxCount];
-    __shared__ int s_pieces[kMaxCount], s_npf[kMaxCount], s_E[kMaxCount], s_f[kMaxCount];
+    // s_key: size keys, then the ranks' prefix sum of update pieces; s_first:
+    // that of slabs
+    __shared__ Rank s_rank[kMaxCount];
+    __shared__ int64_t s_key[kMaxCount], s_scan[kMaxCount / kWave], s_first[kMaxCount];
+    __shared__ int s_ord[kMaxCount];
     __shared__ unsigned s_err;
-    __shared__ int s_total;
+    __shared__ int64_t s_total, s_groups;
     const int tid = threadIdx.x;
     if (tid == 0) s_err = 0u;
     __syncthreads();
-    tsg_orth_desc x{};
+    int64_t key = -1;
     if (tid < count) {
-        x = in[tid];
+        const tsg_orth_desc x = in[tid];
         const uintptr_t al = reinterpret_cast<uintptr_t>(x.V) | reinterpret_cast<uintptr_t>(x.W) |
                              reinterpret_cast<uintptr_t>(x.C);
-        bool ok = x.K >= 0 && x.M >= 1 && x.N >= 1 && x.M <= kMaxM && x.N <= kMaxN && x.ldv >= x.M &&
-                  x.ldw >= x.N && x.ldc >= x.N && x.C && (x.K == 0 || (x.V && x.W)) && al % sizeof(double) == 0;
-        const int64_t R = ok ? slab_rows(x.K, x.M, x.N, x.ldv, x.ldw, rows_fixed, item_bytes) : 0;
-        const int64_t nsl = x.K > 0 && R > 0 ? (x.K + R - 1) / R : 1;  // K = 0: one empty slab sets C = 0
-        ok = ok && R > 0 && nsl <= ((int64_t)1 << 24);
+        const bool ok = x.K >= 0 && x.M >= 1 && x.N >= 1 && x.M <= kMaxM && x.N <= kMaxN && x.ldv >= x.M &&
+                        x.ldw >= x.N && x.ldc >= x.N && x.C && (x.K == 0 || (x.V && x.W)) && al % sizeof(double) == 0;
         if (!ok) atomicOr(&s_err, kErrDesc);
-        s_key[tid] = x.K * (int64_t)(x.M + x.N);
-        s_rows[tid] = ok ? R : 1;
-        s_nsl[tid] = ok ? (int)nsl : 1;
-        s_E[tid] = x.M * x.N;
+        key = ok ? x.K * (int64_t)(x.M + x.N) : 0;
+        s_key[tid] = key;
         flags[tid] = 0u;           // arrival counter
         flags[count + tid] = 0u;   // ready flag
     }
@@ -832,54 +949,72 @@ orth_setup(const tsg_orth_desc* __restrict__ in, int count, int64_t rows_fixed, 
     // rank by decreasing size, ties by index
     if (tid < count) {
         int r = 0;
-        for (int j = 0; j < count; ++j) r += (s_key[j] > s_key[tid]) || (s_key[j] == s_key[tid] && j < tid);
+        for (int j = 0; j < count; ++j) r += (s_key[j] > key) || (s_key[j] == key && j < tid);
         s_ord[r] = tid;
     }
+    if (tid == kMaxCount - 1) s_total = 0;
     __syncthreads();
-    if (tid < count) s_key[tid] = x.K;  // the keys are no longer needed
+    const int64_t sum = block_scan(key > 0 ? key : 0, s_scan);
+    if (tid == kMaxCount - 1) s_total = sum;
     __syncthreads();
-    if (tid == 0) {
-        // update pieces per instance, from the end of the queue backwards
-        int64_t made = 0;
-        for (int r = count - 1; r >= 0; --r) {
-            const int i = s_ord[r];
-            const int64_t K = s_key[i], R = s_rows[i];
-            const int n = s_nsl[i];
-            int64_t pieces = 0, npf = 1;
-            const int f = rows_fixed > 0 ? 1 : made < resident ? 4 : made < 3 * (int64_t)resident ? 2 : 1;
-            if (K > 0) {
-                const int64_t last = K - (int64_t)(n - 1) * R;
-                const int64_t pf = update_piece(R, f), pl = update_piece(last, f);
-                npf = (R + pf - 1) / pf;
-                pieces = (int64_t)(n - 1) * npf + (last + pl - 1) / pl;
-            }
-            s_pieces[i] = (int)min(pieces, (int64_t)1 << 30);
-            s_npf[i] = (int)npf;
-            s_f[i] = f;
-            made += pieces;
-        }
-        // queue positions and partial-sum offsets, largest instance first
-        if (lag < 1) lag = 1;
-        int64_t pos = 0, part = 0;
-        for (int r = 0; r < count + lag; ++r) {
-            if (r < count) {
-                const int i = s_ord[r];
-                s_part0[i] = part;
-                part += (int64_t)s_nsl[i] * s_E[i];
-                s_pos1[i] = (int)min(pos, (int64_t)1 << 30);
-                pos += s_nsl[i];
-            }
-            if (r >= lag && r - lag < count) {
-                const int i = s_ord[r - lag];
-                s_pos2[i] = (int)min(pos, (int64_t)1 << 30);
-                pos += s_pieces[i];
+    const int64_t input = 8 * s_total;
+    int64_t bytes = slab_bytes(input, count, item_bytes);
+    // from here on thread r holds the instance of rank r
+    const bool mine = tid < count;
+    const int i = mine ? s_ord[tid] : 0;
+    const bool bad = s_err != 0u;
+    tsg_orth_desc x{};
+    if (mine && !bad) x = in[i];
+    const int64_t E = (int64_t)x.M * x.N;
+    int64_t R = 1, nsl = 0, part_end = 0, parts = 0;
+    while (true) {
+        if (mine && !bad) {
+            R = slab_rows(x.M, x.N, x.ldv, x.ldw, rows_fixed, bytes);
+            nsl = x.K > 0 && R > 0 ? (x.K + R - 1) / R : 1;  // K = 0: one empty slab sets C = 0
+            if (R <= 0 || nsl > ((int64_t)1 << 24)) {
+                atomicOr(&s_err, kErrDesc);
+                R = nsl = 1;
             }
         }
-        if (pos > max_items || part > max_parts) s_err |= kErrSpace;
-        s_total = s_err ? 0 : (int)pos;
+        parts = mine ? part_doubles(nsl, E) : 0;
+        part_end = block_scan(parts, s_scan);
+        __syncthreads();
+        if (tid == kMaxCount - 1) s_total = part_end;
+        __syncthreads();
+        if (s_total <= max_parts || rows_fixed > 0 || bytes >= input) break;
+        bytes *= 2;
+        __syncthreads();
     }
+    const bool space = s_total <= max_parts;
     __syncthreads();
-    if (tid < count) {
+    const int64_t slab_end = block_scan(nsl, s_scan);
+    __syncthreads();
+    if (tid == kMaxCount - 1) s_total = slab_end;
+    s_first[tid] = slab_end;
+    __syncthreads();
+    // update pieces: finer ones towards the end of the queue
+    const int64_t later = s_total - slab_end;
+    const int f = rows_fixed > 0 || bytes < item_bytes ? 1 : 4 * later < resident ? 4 : 4 * later < 5 * (int64_t)resident ? 2 : 1;
+    int64_t pieces = 0;
+    int npf = 1;
+    if (mine && x.K > 0) {
+        const int64_t last = x.K - (nsl - 1) * R, pf = update_piece(R, f), pl = update_piece(last, f);
+        npf = (int)((R + pf - 1) / pf);
+        pieces = (nsl - 1) * npf + (last + pl - 1) / pl;
+    }
+    const int64_t piece_end = block_scan(pieces, s_scan);
+    s_key[tid] = piece_end;
+    const int ng = mine ? (int)((nsl + kGroup - 1) / kGroup) : 0;
+    const int64_t group_end = block_scan(ng, s_scan);
+    if (tid == kMaxCount - 1) s_groups = group_end;
+    __syncthreads();
+    if (lag < 1) lag = 1;
+    const int64_t total = s_first[kMaxCount - 1] + s_key[kMaxCount - 1];
+    const bool fits = space && total <= max_items && total < ((int64_t)1 << 30);
+    if (tid == 0 && !fits) atomicOr(&s_err, kErrSpace);
+    __syncthreads();
+    if (mine && s_err == 0u) {
+        const int64_t part0 = part_end - parts;
         DevDesc d{};
         d.K = x.K;
         d.V = x.V;
@@ -890,47 +1025,53 @@ orth_setup(const tsg_orth_desc* __restrict__ in, int count, int64_t rows_fixed, 
         d.ldc = x.ldc;
         d.M = x.M;
         d.N = x.N;
-        d.part0 = s_part0[tid];
-        d.nparts = s_nsl[tid];
-        dd[tid] = d;
+        d.part0 = part0;
+        d.nparts = (int)nsl;
+        d.group0 = (int)(group_end - ng);
+        dd[i] = d;
+        // positions: before rank r's slabs come the updates of ranks below
+        // r - lag, before its updates the slabs of ranks up to r + lag
+        const int64_t before1 = tid - lag > 0 ? s_key[tid - lag - 1] : 0;
+        const int64_t before2 = s_first[tid + lag < count ? tid + lag : kMaxCount - 1];
+        s_rank[tid] = Rank{x.K, R, part0, (int)nsl, (int)pieces, npf, i, f, (int)E,
+                           (int)(slab_end - nsl + before1), (int)(piece_end - pieces + before2)};
     }
-    if (s_total > 0) {
-        for (int r = 0; r < count; ++r) {
-            const int i = s_ord[r];
-            const int64_t K = s_key[i], R = s_rows[i];
-            const int n = s_nsl[i];
-            const int64_t E = s_E[i];
-            for (int j = tid; j < n; j += blockDim.x) {
+    __syncthreads();
+    if (s_err == 0u) {
+        for (int g = tid; g < (int)s_groups; g += kMaxCount) groups[g] = 0u;
+        const int lane = tid & (kWave - 1);
+        for (int r = tid / kWave; r < count; r += kMaxCount / kWave) {
+            const Rank k = s_rank[r];
+            for (int j = lane; j < k.slabs; j += kWave) {
                 Item it{};
-                it.row0 = (int64_t)j * R;
-                it.nrows = (int32_t)min(R, K - it.row0);
-                it.inst = i;
+                it.row0 = j * k.rows;
+                it.nrows = (int32_t)min(k.rows, k.K - it.row0);
+                it.inst = k.inst;
                 it.phase = 1;
-                it.slot_off = s_part0[i] + j * E;
-                items[s_pos1[i] + j] = it;
+                it.slab = j;
+                it.slot_off = k.part0 + (int64_t)j * k.E;
+                items[k.pos1 + j] = it;
             }
-            const int npf = s_npf[i];
-            const int64_t full = (int64_t)(n - 1) * npf;
-            for (int p = tid; p < s_pieces[i]; p += blockDim.x) {
-                const int j = p < full ? p / npf : n - 1;
-                const int64_t k = p < full ? p - (int64_t)j * npf : p - full;
-                const int64_t row0 = (int64_t)j * R, nr = min(R, K - row0);
-                const int64_t piece = update_piece(nr, s_f[i]);
+            const int full = (k.slabs - 1) * k.npf;
+            for (int p = lane; p < k.pieces; p += kWave) {
+                const int j = p < full ? p / k.npf : k.slabs - 1, c = p < full ? p - j * k.npf : p - full;
+                const int64_t row0 = j * k.rows, nr = min(k.rows, k.K - row0), piece = update_piece(nr, k.f);
                 Item it{};
-                it.row0 = row0 + k * piece;
-                it.nrows = (int32_t)min(piece, nr - k * piece);
-                it.inst = i;
+                it.row0 = row0 + c * piece;
+                it.nrows = (int32_t)min(piece, nr - c * piece);
+                it.inst = k.inst;
                 it.phase = 2;
-                items[s_pos2[i] + p] = it;
+                items[k.pos2 + p] = it;
             }
         }
     }
-    if (tid == 0) {
+    if (tid == kMaxCount - 1) {
         ctrl->head = 0u;
         ctrl->done = 0u;
         ctrl->err = s_err;
         ctrl->spin = spin;
-        ctrl->total = (unsigned)s_total;
+        ctrl->total = s_err ? 0u : (unsigned)total;
+        ctrl->groups = (unsigned)group_end;
     }
 }
 
@@ -1003,7 +1144,7 @@ hipError_t launch_setup(const tsg_orth_desc* d_in, int count, int64_t rows_fixed
 {
     hipLaunchKernelGGL(orth_setup, dim3(1), dim3(kMaxCount), 0, s, d_in, count, rows_fixed, item_bytes(), lag,
                        resident, kDefaultSpin, at<Ctrl>(ws, L.ctrl), at<DevDesc>(ws, L.descs), at<unsigned>(ws, L.flags),
-                       at<Item>(ws, L.items), L.max_items, L.max_parts);
+                       at<unsigned>(ws, L.groups), at<Item>(ws, L.items), L.max_items, L.max_parts);
     return hipGetLastError();
 }
 
@@ -1011,8 +1152,8 @@ hipError_t launch_persistent(void* ws, const Layout& L, int count, int grid, hip
 {
     unsigned* flags = at<unsigned>(ws, L.flags);
     hipLaunchKernelGGL(orth_persistent, dim3(grid), dim3(kThreads), 0, s, at<DevDesc>(ws, L.descs),
-                       at<Item>(ws, L.items), at<double>(ws, L.parts), flags, flags + count, at<Ctrl>(ws, L.ctrl),
-                       count);
+                       at<Item>(ws, L.items), at<double>(ws, L.parts), flags, flags + count, at<unsigned>(ws, L.groups),
+                       at<Ctrl>(ws, L.ctrl), count);
     return hipGetLastError();
 }
 
@@ -1060,7 +1201,10 @@ tsg_status tsg_orth_plan_create(tsg_orth_plan* plan, int32_t count, const tsg_or
     *plan = nullptr;
     if (!descs || count < 1) return fail(TSG_E_ARG, "need count >= 1 descriptors (count %lld)", count);
     if (count > kMaxCount) return fail(TSG_E_UNSUPPORTED, "at most %lld instances per plan", kMaxCount);
-    int64_t slabs = 0, parts = 0;
+    int64_t slabs = 0, parts = 0, input = 0;
+    for (int i = 0; i < count; ++i)
+        if (descs[i].K > 0 && descs[i].M > 0 && descs[i].N > 0) input += 8 * descs[i].K * (int64_t)(descs[i].M + descs[i].N);
+    const int64_t slab_size = slab_bytes(input, count, item_bytes());
     for (int i = 0; i < count; ++i) {
         const tsg_orth_desc& s = descs[i];
         if (s.K < 0 || s.M < 1 || s.N < 1) return fail(TSG_E_ARG, "instance %lld: K < 0, M < 1 or N < 1", i);
@@ -1072,14 +1216,14 @@ tsg_status tsg_orth_plan_create(tsg_orth_plan* plan, int32_t count, const tsg_or
         if ((reinterpret_cast<uintptr_t>(s.V) | reinterpret_cast<uintptr_t>(s.W) |
              reinterpret_cast<uintptr_t>(s.C)) % sizeof(double))
             return fail(TSG_E_ARG, "instance %lld: pointer not aligned to 8 bytes", i);
-        const int64_t R = slab_rows(s.K, s.M, s.N, s.ldv, s.ldw, rows_per_item, item_bytes());
+        const int64_t R = slab_rows(s.M, s.N, s.ldv, s.ldw, rows_per_item, slab_size);
         if (R < 1)
             return fail(TSG_E_UNSUPPORTED, "instance %lld: slab height must be in [1, %lld] for its leading dimensions",
                         i, slab_limit(s.ldv, s.ldw));
         const int64_t nslab = s.K > 0 ? (s.K + R - 1) / R : 1;
         if (nslab > ((int64_t)1 << 24)) return fail(TSG_E_UNSUPPORTED, "instance %lld: too many slabs", i);
         slabs += nslab;
-        parts += nslab * s.M * s.N;
+        parts += part_doubles(nslab, (int64_t)s.M * s.N);
     }
     // at most four update pieces per slab
     if (5 * slabs > ((int64_t)1 << 30)) return fail(TSG_E_UNSUPPORTED, "too many work items");
@@ -1097,7 +1241,7 @@ tsg_status tsg_orth_plan_create(tsg_orth_plan* plan, int32_t count, const tsg_or
         free_plan(p);
         return fail(TSG_E_NOMEM, "device allocation of the plan failed");
     }
-    const Ctrl ctrl0{0u, 0u, 0u, kDefaultSpin, 0u, {0u, 0u, 0u}};
+    const Ctrl ctrl0{0u, 0u, 0u, kDefaultSpin, 0u, 0u, {0u, 0u}};
     if (hipMemcpy(p->d_in, descs, sizeof(tsg_orth_desc) * count, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(at<Ctrl>(p->ws, p->L.ctrl), &ctrl0, sizeof(Ctrl), hipMemcpyHostToDevice) != hipSuccess ||
         launch_setup(p->d_in, count, rows_per_item, queue_lag(count), (int)resident, p->ws, p->L, nullptr) !=
@@ -1197,8 +1341,12 @@ namespace tsg {
 size_t orth_workspace_size(int64_t K, int32_t M, int32_t N, int32_t count)
 {
     if (K < 0 || M < 1 || N < 1 || M > kMaxM || N > kMaxN || count < 1 || count > kMaxCount) return 0;
-    const int64_t R = slab_rows(K, M, N, M, N, 0, item_bytes());
-    const int64_t nslab = K > 0 && R > 0 ? (K + R - 1) / R : 1;
-    return make_layout(count, kItemsPerInstance * count, (int64_t)count * nslab * M * N).bytes;
+    // slabs of the full size, at most kMaxSlabs an instance, or kTargetSlabs
+    // and the rest of each instance's last
+    const int64_t R = slab_rows(M, N, M, N, 0, item_bytes());
+    const int64_t nslab = std::min(kMaxSlabs, K > 0 && R > 0 ? (K + R - 1) / R : 1);
+    const int64_t E = (int64_t)M * N, full = part_doubles(nslab * count, E) + count * E;
+    const int64_t small = part_doubles(kTargetSlabs, E) + 2 * count * E;
+    return make_layout(count, kItemsPerInstance * count, full > small ? full : small).bytes;
 }
 }  // namespace tsg
