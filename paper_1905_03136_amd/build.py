@@ -33,7 +33,7 @@ CFLAGS = [
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 
-# The kernels that stage their rows in LDS: FP64 matrix-core results in
+# The kernels that bring their rows straight into LDS: FP64 matrix-core results in
 # architectural registers.  With C and D in accumulation registers a 16x16x4
 # product takes 104 (two waves a SIMD) to 141 cycles (one) instead of 65:
 # register-only loops reach 38-52 and 77 TF/s.
@@ -41,8 +41,8 @@ STAGE_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 
 # headers every unit includes; the C ABI header only the hand-written units
 HEADERS = [os.path.join(CSRC, h) for h in ("tsg_device.hpp", "tsg_kernels.hpp", "tsg_registry.hpp")]
-# header of the units that hold kernels staging their rows in LDS
-STAGE_HEADER = os.path.join(CSRC, "tsg_stage.hpp")
+# headers of the units that hold kernels bringing their rows straight into LDS
+STAGE_HEADERS = [os.path.join(CSRC, h) for h in ("tsg_stage.hpp", "tsg_once.hpp")]
 ABI_HEADER = os.path.join(ROOT, "include", "tsgemm.h")
 TUNE_LIB = os.path.join(HERE, "libtsgemm_tune.so")
 # builds of other variant sets (the autotuner's libraries): generated sources
@@ -205,10 +205,11 @@ def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, l
 
     def staged(s):
         with open(s) as f:
-            return '#include "tsg_stage.hpp"' in f.read()
+            text = f.read()
+        return '#include "tsg_stage.hpp"' in text or '#include "tsg_once.hpp"' in text
 
     def deps(s):
-        return [s] + HEADERS + ([STAGE_HEADER] if staged(s) else []) + ([] if s in units else [ABI_HEADER])
+        return [s] + HEADERS + (STAGE_HEADERS if staged(s) else []) + ([] if s in units else [ABI_HEADER])
 
     def compile_all(sources, what):
         todo = [(s, obj_of[s]) for s in sources

@@ -14,7 +14,6 @@ run-time-width variants of the same templates, which keep the guards.
 A configuration can be overridden by the autotuner's table (``tuned.json``).
 """
 import json
-import math
 import os
 
 # storage types of the tall matrices: (ABI id, complex).  r32 / c64 are the
@@ -709,6 +708,91 @@ def stage_variants(tuned_path=None):
             for dt, wm, q, sym, gauss in stage_classes()]
 
 
+# TSMM of one small tile a wave (tsmm_once): contraction depths of MS slices of
+# four columns of A times groups of four columns of B
+ONCE_MS = (1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16)
+ONCE_QUADS = (1, 2, 4, 5, 6, 7, 8, 10, 12, 14, 16)
+
+
+def once_config(dt, ms, quads, U, CL, OCC, W, DB=0):
+    """Configuration of tsmm_once for ms slices and `quads` groups: 16 U rows a
+    wave, C in LDS (CL) or in registers, OCC waves a SIMD at least, W waves a
+    block; DB: persistent blocks, two tiles of a wave in LDS."""
+    return dict(kind="once", MS=ms, NB=quads // 4, NQ=quads % 4, U=U, CL=CL, OCC=OCC, WPB=W, DB=DB)
+
+
+def once_c_bytes(dt, c):
+    """LDS bytes of the block's copy of C."""
+    np_ = 16 * c["NB"] + 4 * c["NQ"]
+    cld = np_ if DTYPES[dt][1] else np_ + (48 - np_ % 32) % 32
+    return 4 * c["MS"] * cld * (16 if DTYPES[dt][1] else 8) if c["CL"] else 0
+
+
+def once_candidates(dt, ms, quads):
+    """Configurations the autotuner times for one class: tiles of 1 to 8 KB of
+    the wider matrix a wave, C in registers where it takes at most 24 of them
+    a lane (in binary64 units) and in LDS from 4 on."""
+    cplx = DTYPES[dt][1]
+    cw, es = (2 if cplx else 1), (2 if cplx else 1) * (4 if is_f32(dt) else 8)
+    groups = quads // 4 + quads % 4
+    out = []
+    for u in (1, 2, 4, 8):
+        tile = 16 * u * 4 * max(ms, quads) * es
+        if tile > 8192 * (2 if u == 1 else 1) or (tile < 1024 and u < 8):
+            continue
+        acc = u * (4 * (quads // 4) + quads % 4) * cw
+        for cl in (0, 1):
+            creg = 0 if cl else ms * groups * cw
+            if creg > 24 or (cl and ms * groups * cw < 4):
+                continue
+            for occ in (2, 4):
+                # registers in binary64 units: accumulators, C, operands, addresses
+                regs = acc + creg + 2 * cw * u + 12
+                if regs > (120 if occ == 2 else 60) or (occ == 2 and regs <= 44):
+                    continue
+                for w in (4, 8, 16) if cl else (4,):
+                    c = once_config(dt, ms, quads, u, cl, occ, w)
+                    cb = once_c_bytes(dt, c)
+                    wb = w * (-(-tile // 1024) * 1040 + 256)
+                    if w > 4 * occ:
+                        continue
+                    if cb + wb <= LDS_BYTES and (w == 4 or cb >= 2048 * w // 4):
+                        out.append(c)
+                    # persistent blocks: where C is large
+                    blocks = LDS_BYTES // (cb + 2 * wb)
+                    if cl and w < 16 and ms * quads >= 36 and blocks and blocks * w >= 4 * occ / 2:
+                        out.append(once_config(dt, ms, quads, u, cl, occ, w, 1))
+    return out
+
+
+def once_above(v):
+    """Widths of the next smaller classes: a class serves the widths above them."""
+    m, n = v["maxM"] // 4, v["maxN"] // 4
+    return 4 * max([0] + [x for x in ONCE_MS if x < m]), 4 * max([0] + [x for x in ONCE_QUADS if x < n])
+
+
+def once_classes():
+    return [(dt, ms, q) for dt in STAGE_DTYPES for ms in ONCE_MS for q in ONCE_QUADS]
+
+
+def tuned_once(path=None):
+    """{(dtype, slices, groups): configuration} of the classes for which the
+    autotuner found tsmm_once the fastest (tuned.json key "once")."""
+    path = path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned.json")
+    out = {}
+    if os.path.exists(path):
+        with open(path) as f:
+            for e in json.load(f).get("once", []):
+                cfg = once_config(*(e[k] for k in ("dt", "ms", "quads", "U", "CL", "OCC", "W", "DB")))
+                out[(e["dt"], e["ms"], e["quads"])] = dict(cfg, full=e["full"])
+    return out
+
+
+def once_variants(tuned_path=None):
+    return [dict(op="tsmm", dt=dt, M=0, N=0, maxM=4 * ms, maxN=4 * q, cfg=cfg)
+            for (dt, ms, q), cfg in sorted(tuned_once(tuned_path).items())]
+
+
 def stage_classes():
     """(dtype, column blocks, groups of four columns, a matrix with itself,
     three-product form) of every kernel of stage_variants."""
@@ -788,7 +872,7 @@ def load_tuned(path):
 def needs_layout(cfg):
     """True if a configuration reads A in a way only some layouts allow
     (paired loads, slab reads, direct loads of whole stages into LDS)."""
-    return bool(cfg.get("VA") or cfg.get("FL") or cfg.get("kind") in ("lds", "dot", "stage"))
+    return bool(cfg.get("VA") or cfg.get("FL") or cfg.get("kind") in ("lds", "dot", "stage", "once"))
 
 
 def exact_variants(widths, tuned=None):
@@ -832,6 +916,8 @@ def variant_name(v):
         tag = "a32_b%dx%dw%d_u%d" % (c["MB"], c["NB"], c["MW"], c["U"])
     elif c["kind"] == "a32":
         tag = "a32_s%dn%d_u%d" % (c["MS"], c["NB"], c["U"])
+    elif c["kind"] == "once":
+        tag = "mfma_once_u%d%s%s" % (c["U"], "_cl" if c["CL"] else "", "_db" if c["DB"] else "")
     elif c["kind"] == "stage":
         tag = "lds_%s_k%d_s%d" % ("sym" if c.get("SYM") else "dma", c["RT"], c["NS"])
         if c["KG"] != 1:
@@ -873,6 +959,10 @@ def _template(v):
     f32 = "true" if is_f32(v["dt"]) else "false"
     if c["kind"] == "packed":
         return "tsg::%s_packed<%d, %d, %d, %s, %d, %d, %s>" % (v["op"], M, N, c["U"], cplx, c["WPB"], nbuf, f32)
+    if c["kind"] == "once":
+        return "tsg::tsmm_once<%d, %d, %d, %d, %d, %s, %s, %s, %s, %d>" % (
+            c["MS"], c["NB"], c["NQ"], c["U"], c["WPB"], cplx, f32, "true" if c["CL"] else "false",
+            "true" if c["DB"] else "false", c["OCC"])
     if c["kind"] == "stage":
         return "tsg::tsmttsm_stage<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, %d>" % (
             c["NB"], c["NQ"], c["WM"], c["KG"], c["RT"], c["NS"], cplx, f32, "true" if c.get("G3") else "false",
@@ -926,6 +1016,16 @@ def rows_per_tile(v):
 def _launcher(v, fn):
     tmpl = _template(v)
     threads = 64 * v["cfg"]["WPB"]
+    if v["cfg"]["kind"] == "once":
+        es = (2 if DTYPES[v["dt"]][1] else 1) * (4 if is_f32(v["dt"]) else 8)
+        return ("void %s(const tsg::Launch& p)\n{\n"
+                "    const uint32_t ra = (uint32_t)p.M * %d, rb = (uint32_t)p.N * %d;  // bytes of a row\n"
+                "    hipLaunchKernelGGL((%s), dim3(p.grid), dim3(%d), p.lds, p.stream, p.K, p.M, p.N, p.A, p.lda,\n"
+                "                       static_cast<const double*>(p.X), p.ldx, p.Y, p.ldy, p.alpha, p.beta, p.conj, p.opc,\n"
+                "                       (uint32_t)(((1ull << 32) + ra - 1) / ra), (uint32_t)(((1ull << 32) + rb - 1) / rb),\n"
+                "                       (int)tsg::once_wave_bytes(p.M, p.N, %d, %d, p.beta != 0.0));\n}\n"
+                "const void* %s() { return reinterpret_cast<const void*>(&%s); }\n"
+                % (fn, es, es, tmpl, threads, es, 16 * v["cfg"]["U"], fn.replace("launch_", "kernel_"), tmpl))
     if v["cfg"]["kind"] == "stage":
         # the wider matrix is the kernel's X
         return ("void %s(const tsg::Launch& p)\n{\n    const bool swap = p.M < p.N;\n"
@@ -957,12 +1057,14 @@ def _record(v, fn):
     flat_a = int(bool(c.get("FL")) or c["kind"] in ("lds", "dot"))
     read_b = int(bool(c.get("RB")))
     align16 = int(c["kind"] in ("lds", "dot"))
-    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s, %d, %d, %d, %d},\n'
+    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d},\n'
             % (OPS[v["op"]], DTYPES[v["dt"]][0], v["M"], v["N"], v["maxM"], v["maxN"], pair_a, pair_x, even,
                64 * c["WPB"], rows_per_tile(v), pack, flat_a, read_b, align16, variant_name(v),
                fn.replace("launch_", "kernel_"), fn, 0 if c["kind"] != "stage" else 2 if c.get("SYM") else 1,
                c.get("NS", 0), int(c["kind"] == "stage" and bool(c.get("G3"))),
-               stage_fold(v["dt"], c) if c["kind"] == "stage" else 0))
+               stage_fold(v["dt"], c) if c["kind"] == "stage" else 0, 16 * c["U"] if c["kind"] == "once" else 0,
+               once_c_bytes(v["dt"], c) if c["kind"] == "once" else 0, c.get("DB", 0),
+               *(once_above(v) if c["kind"] == "once" else (0, 0)), c.get("full", 1)))
 
 
 # batched orthogonalisation: input bytes per slab and queue interleave (0: every
@@ -992,13 +1094,14 @@ def emit(outdir, variants, per_file=6, exclude=(), batched=None):
     files = []
     recs = []
     decls = []
-    # the kernels that stage their rows in LDS have units of their own (other
-    # compiler flags, see build.STAGE_FLAGS)
-    staged = [v for v in variants if v["cfg"]["kind"] == "stage"]
-    other = [v for v in variants if v["cfg"]["kind"] != "stage"]
-    chunks = [vs[i:i + per_file] for vs in (other, staged) for i in range(0, len(vs), per_file)] or [[]]
+    # the kernels that bring their rows straight into LDS have units of their
+    # own (other compiler flags, see build.STAGE_FLAGS)
+    kinds = [[v for v in variants if (v["cfg"]["kind"] if v["cfg"]["kind"] in ("stage", "once") else "") == k]
+             for k in ("", "stage", "once")]
+    chunks = [vs[i:i + per_file] for vs in kinds for i in range(0, len(vs), per_file)] or [[]]
     for fi, chunk in enumerate(chunks):
-        head = "tsg_stage.hpp" if chunk and chunk[0]["cfg"]["kind"] == "stage" else "tsg_kernels.hpp"
+        head = {"stage": "tsg_stage.hpp", "once": "tsg_once.hpp"}.get(chunk[0]["cfg"]["kind"] if chunk else "",
+                                                                     "tsg_kernels.hpp")
         body = ['// generated by codegen.py -- do not edit\n#include "%s"\n' % head +
                 '#include "tsg_registry.hpp"\n\nnamespace tsg_gen {\n']
         for k, v in enumerate(chunk):
@@ -1051,7 +1154,8 @@ def all_variants(widths=None, tuned_path=None):
         if (M, N) not in seen:
             seen.add((M, N))
             uniq.append((M, N))
-    return exact_variants(uniq, load_tuned(tuned_path)) + generic_variants(tuned_path) + stage_variants(tuned_path)
+    return (exact_variants(uniq, load_tuned(tuned_path)) + generic_variants(tuned_path) + stage_variants(tuned_path)
+            + once_variants(tuned_path))
 
 
 def template_of(v):

@@ -54,6 +54,13 @@ struct Variant {
     int stages;         // its stages in LDS
     int gauss;          // it forms complex products from three real ones
     int fold;           // LDS bytes of its sum over row groups
+    // TSMM of one small tile a wave (run-time widths): rows of a wave's tile
+    // (0: not such a kernel), LDS bytes of its copy of C
+    int once;
+    int once_c;
+    int once_db;  // two tiles of a wave in LDS, persistent blocks
+    int once_m, once_n;  // it serves widths above these: those of the next smaller class
+    int once_full;       // and its largest widths (0: another kernel is faster at just those)
 };
 
 // LDS bytes of a block of the staged kernel: NS stages of RT rows of both
@@ -65,6 +72,15 @@ inline size_t stage_lds_bytes(int wide, int narrow, size_t es, int RT, int NS, b
     const size_t x = (wide * es * RT + 1023) / 1024, y = sym ? 0 : (narrow * es * RT + 1023) / 1024;
     const size_t b = (x + y) * 1024 * NS + 1024;
     return b > fold ? b : fold;
+}
+
+// LDS bytes of a wave of the one-tile kernel: the tile's rows of A, then of B,
+// in pieces of 1 KB 16 bytes apart (and room for reads of columns past a
+// width); with beta != 0 the old rows of B too.
+inline size_t once_wave_bytes(int M, int N, size_t es, int rows, bool beta_nz)
+{
+    const size_t a = (M * es * rows + 1023) / 1024 * 1040, b = (N * es * rows + 1023) / 1024 * 1040;
+    return (a > b ? a : b) + 256 + (beta_nz ? b + 256 : 0);
 }
 
 extern const Variant kVariants[];

@@ -308,6 +308,50 @@ const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda,
     return nullptr;
 }
 
+constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
+
+// LDS bytes of a block that the launch asks for (kernels with run-time sizes).
+size_t lds_for(const tsg::Variant& v, int M, int N, bool beta_nz = false)
+{
+    const size_t es = elem_bytes((tsg_dtype)v.dt);
+    if (v.once) return v.once_c + (v.once_db ? 2 : 1) * (v.threads / 64) * tsg::once_wave_bytes(M, N, es, v.once, beta_nz);
+    if (!v.stage) return 0;
+    const int wide = M > N ? M : N, narrow = M > N ? N : M;
+    return tsg::stage_lds_bytes(wide, narrow, es, v.rows_per_tile, v.stages, v.stage == 2, v.fold);
+}
+
+// The same for the one-tile kernel of TSMM (its tile: v.once rows): contiguous
+// rows or whole 16-byte chunks, widths that fill its slices and groups but for
+// the last (it masks no others, and a class that is not in the table was
+// slower than the kernels below, so no larger one stands in for it), tiles
+// that fit LDS (with beta != 0 the old rows too).
+bool once_serves(const tsg::Variant& v, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb,
+                 bool beta_nz)
+{
+    if (M > v.maxM || N > v.maxN || M <= v.once_m || N <= v.once_n) return false;
+    const size_t es = elem_bytes((tsg_dtype)v.dt);
+    auto reads = [&](int W, const void* p, int64_t ld) {
+        return aligned(p, 16) && (ld == W || (W * es % 16 == 0 && ld * es % 16 == 0 &&
+                                              ld < (int64_t)((size_t)1 << 31) / (int64_t)(es * v.once)));
+    };
+    return reads(M, A, lda) && reads(N, B, ldb) && lds_for(v, M, N, beta_nz) <= kLdsBytes;
+}
+
+const tsg::Variant* pick_once(int dt, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb,
+                              bool beta_nz)
+{
+    // the narrow non-square pairs in binary64 have kernels of their exact
+    // widths, which multiply no zeros (2^22 rows, 4 x 8: 71 us there, 69 here;
+    // 4 x 4, on the matrix cores both times: 52 and 46)
+    if (M <= 8 && N <= 8 && M != N && (dt == TSG_R64 || dt == TSG_C128)) return nullptr;
+    for (int i = 0; i < tsg::kNumVariants; ++i) {
+        const tsg::Variant& v = tsg::kVariants[i];
+        if (v.once && v.dt == dt && once_serves(v, M, N, A, lda, B, ldb, beta_nz))
+            return v.once_full || M < v.maxM || N < v.maxN ? &v : nullptr;
+    }
+    return nullptr;
+}
+
 const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_t lda, const void* X,
                              int64_t ldx, bool beta_nz)
 {
@@ -322,6 +366,7 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
             const tsg::Variant& v = tsg::kVariants[i];
             if (g_force != v.name) continue;
             if (v.stage) return v.op == op && v.dt == dt && stage_serves(v, M, N, A, lda, X, ldx) ? &v : nullptr;
+            if (v.once) return v.op == op && v.dt == dt && once_serves(v, M, N, A, lda, X, ldx, beta_nz) ? &v : nullptr;
             const bool serves = (v.M == M && v.N == N) || (v.M == 0 && M <= v.maxM && N <= v.maxN);
             if (v.op == op && v.dt == dt && serves && (!v.pairA || a_pairs) && (!v.pairX || x_pairs) &&
                 (!v.flatA || rows_contiguous) && (!v.readB || beta_nz) && (!v.align16 || ax16))
@@ -331,9 +376,11 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
     }
     if (op == tsg::OP_TSMTTSM)
         if (const tsg::Variant* v = pick_stage(dt, M, N, A, lda, X, ldx)) return v;
+    if (op == tsg::OP_TSMM)
+        if (const tsg::Variant* v = pick_once(dt, M, N, A, lda, X, ldx, beta_nz)) return v;
     for (int i = 0; i < tsg::kNumVariants; ++i) {
         const tsg::Variant& v = tsg::kVariants[i];
-        if (v.op != op || v.dt != dt || v.stage) continue;
+        if (v.op != op || v.dt != dt || v.stage || v.once) continue;
         if (v.pairA && !a_pairs) continue;
         if (v.pairX && !x_pairs) continue;
         if (v.flatA && !rows_contiguous) continue;
@@ -406,16 +453,7 @@ tsg_status validate(tsg_dtype dt, int64_t K, int32_t M, int32_t N, const void* A
     return TSG_OK;
 }
 
-// LDS bytes of a block that the launch asks for (kernels with run-time sizes).
-size_t lds_for(const tsg::Variant& v, int M, int N)
-{
-    if (!v.stage) return 0;
-    const size_t es = elem_bytes((tsg_dtype)v.dt);
-    const int wide = M > N ? M : N, narrow = M > N ? N : M;
-    return tsg::stage_lds_bytes(wide, narrow, es, v.rows_per_tile, v.stages, v.stage == 2, v.fold);
-}
-
-int grid_for(int dev, const tsg::Variant& v, int64_t K, int M, int N, int cus)
+int grid_for(int dev, const tsg::Variant& v, int64_t K, int M, int N, int cus, bool beta_nz = false)
 {
     if (v.stage == 2) {
         // a matrix with itself: the grid of two matrices of its width, whose
@@ -432,7 +470,10 @@ int grid_for(int dev, const tsg::Variant& v, int64_t K, int M, int N, int cus)
     if (v.pack == 1) rows *= 16 / (M > N ? M : N);
     if (v.pack == 2) rows *= 16 / N;
     const int64_t tiles = (K + rows - 1) / rows;
-    const int64_t cap = (int64_t)cus * occupancy(dev, v, lds_for(v, M, N));
+    // the one-tile kernel of TSMM: a block for every tile
+    const size_t lds = lds_for(v, M, N, beta_nz);
+    const int blocks = v.once && !v.once_db && lds <= (64u << 10) ? 0 : occupancy(dev, v, lds);
+    const int64_t cap = v.once && !v.once_db ? (int64_t)1 << 30 : (int64_t)cus * blocks;
     int64_t g = tiles < cap ? tiles : cap;
     if (v.op == tsg::OP_TSMTTSM) {
         // the per-block partial sums of a launch always fit the no-alloc
@@ -571,7 +612,7 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
                         g_force.empty() ? "" : " (a forced variant does not apply)");
     tsg::Launch p{};
     p.stream = static_cast<hipStream_t>(stream);
-    p.grid = grid_for(dev, *v, K, M, N, di.cus);
+    p.grid = grid_for(dev, *v, K, M, N, di.cus, beta != 0.0);
     p.K = K;
     p.M = M;
     p.N = N;
@@ -585,6 +626,7 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
     p.ldy = ldb;
     p.alpha = alpha;
     p.beta = beta;
+    p.lds = lds_for(*v, M, N, beta != 0.0);
     v->launch(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));

@@ -65,6 +65,14 @@ def cmd_build(args):
         build.build(variants=[v for _, v in stage_tuning_variants()] + codegen.generic_variants(), lib_path=lib,
                     tag="_" + (args.tag or "tune"))
         return
+    if args.once:
+        # the candidates of the one-tile TSMM kernel, and the product's others
+        path = os.path.join(HERE, "tuned.json")
+        widths = codegen.GRADED + codegen.SQUARE_ALL + codegen.NARROW
+        rest = [v for v in codegen.exact_variants(list(dict.fromkeys(widths)), codegen.load_tuned(path))
+                + codegen.generic_variants(path) if v["op"] == "tsmm"]
+        build.build(variants=[v for _, v in once_tuning_variants()] + rest, lib_path=lib, tag="_" + (args.tag or "tune"))
+        return
     if args.generic:
         # the run-time-width classes' candidates (plus the product's own
         # run-time-width variants, so that every pair has a kernel)
@@ -335,6 +343,71 @@ def cmd_stage(args):
         with open(args.out) as f:
             tab = json.load(f)
     tab["stage"] = entries
+    with open(args.out, "w") as f:
+        json.dump(tab, f, indent=1)
+        f.write("\n")
+
+
+def once_tuning_variants():
+    """[(class, variant)] of every candidate of tsmm_once."""
+    from paper_1905_03136_amd import codegen
+    return [(cls, dict(op="tsmm", dt=cls[0], M=0, N=0, maxM=4 * cls[1], maxN=4 * cls[2], cfg=c))
+            for cls in codegen.once_classes() for c in codegen.once_candidates(*cls)]
+
+
+def _other_tsmm(dt, M, N, names):
+    """The TSMM variant the library would pick without tsmm_once (contiguous
+    aligned matrices, beta = 0)."""
+    from paper_1905_03136_amd import codegen
+    path = os.path.join(HERE, "tuned.json")
+    widths = list(dict.fromkeys(codegen.GRADED + codegen.SQUARE_ALL + codegen.NARROW))
+    exact = codegen.exact_variants([(M, N)] if (M, N) in widths else [], codegen.load_tuned(path))
+    for v in exact + codegen.generic_variants(path):
+        if (v["op"], v["dt"]) == ("tsmm", dt) and not v["cfg"].get("RB") and codegen.variant_name(v) in names                 and M <= v["maxM"] and N <= v["maxN"]:
+            return v
+
+
+def cmd_once(args):
+    """GPU: time the candidates of every class of tsmm_once, and the other TSMM
+    kernels the library would pick, on the class's largest widths and on odd
+    ones; classes where tsmm_once is the faster (by the mean over the pairs
+    of time over the other's time, and on the odd widths) go into the table's
+    "once" list, with full = 0 where the other is the faster on the largest."""
+    sys.path.insert(0, ROOT)
+    from paper_1905_03136_amd import build, codegen
+    os.environ.setdefault("TSG_LIBRARY", build.tagged_lib(args.tag))
+    timer = _Timer(args.K, args.warmup, args.reps)
+    groups = {}
+    for cls, v in once_tuning_variants():
+        groups.setdefault(cls, []).append(v)
+    entries = []
+    for cls, vs in groups.items():
+        dt, ms, q = cls
+        by, other = {}, []
+        for M, N in ((4 * ms, 4 * q), (4 * ms - 1, 4 * q - 1)):
+            own = timer.measure("tsmm", dt, M, N, [_other_tsmm(dt, M, N, timer.names)])[0]
+            assert own["ok"], own
+            other.append(own)
+            recs = [r for r in timer.measure("tsmm", dt, M, N, vs) if r.get("us")]
+            assert all(r["ok"] for r in recs), [r["name"] for r in recs if not r["ok"]]
+            for r in recs:
+                by.setdefault(r["name"], []).append((r["us"] / own["us"], r))
+        if not by:
+            continue  # every candidate spills
+        name = min(by, key=lambda n: sum(x for x, _ in by[n]))
+        score = sum(x for x, _ in by[name]) / 2
+        c = by[name][0][1]["cfg"]
+        print("[tune] %-45s %.3f of %s; %s GB/s, other %s" % (
+            name, score, other[0]["name"], [r["GBps"] for _, r in by[name]], [r["GBps"] for r in other]), flush=True)
+        full, odd = (r["us"] / o["us"] for (_, r), o in zip(by[name], other))
+        if score < 0.99 and odd < 1.02:
+            entries.append(dict(dt=dt, ms=ms, quads=q, U=c["U"], CL=c["CL"], OCC=c["OCC"], W=c["WPB"], DB=c["DB"], full=int(full <= 1.0),
+                                score=round(score, 4), other=other[0]["name"]))
+    tab = {"entries": []}
+    if os.path.exists(args.out):
+        with open(args.out) as f:
+            tab = json.load(f)
+    tab["once"] = entries
     with open(args.out, "w") as f:
         json.dump(tab, f, indent=1)
         f.write("\n")
@@ -707,6 +780,7 @@ def main(argv=None):
     b.add_argument("--with-tuned", action="store_true", help="add each width's configuration in tuned.json")
     b.add_argument("--tag", default="", help="build _build/libtsgemm_<tag>.so apart from the default tuning library")
     b.add_argument("--generic", action="store_true", help="the candidates of the run-time-width classes")
+    b.add_argument("--once", action="store_true", help="the candidates of the one-tile TSMM kernel")
     b.add_argument("--stage", action="store_true", help="the candidates of the kernels that stage rows in LDS")
     r = sub.add_parser("run")
     r.add_argument("--widths", default="graded")
@@ -754,6 +828,12 @@ def main(argv=None):
     sg.add_argument("--out", default=os.path.join(HERE, "tuned.json"))
     sg.add_argument("--reps", type=int, default=7)
     sg.add_argument("--warmup", type=int, default=2)
+    on = sub.add_parser("once", help="GPU: configurations of the one-tile TSMM kernel")
+    on.add_argument("--K", type=int, default=1 << 22)
+    on.add_argument("--tag", default="once", help="library built by 'build --once --tag <tag>'")
+    on.add_argument("--out", default=os.path.join(HERE, "tuned.json"))
+    on.add_argument("--reps", type=int, default=7)
+    on.add_argument("--warmup", type=int, default=2)
     t = sub.add_parser("table")
     t.add_argument("--db", default="tune_db.jsonl")
     t.add_argument("--out", default=os.path.join(HERE, "tuned.json"))
@@ -771,6 +851,8 @@ def main(argv=None):
         cmd_heatmap(a)
     elif a.cmd == "stage":
         cmd_stage(a)
+    elif a.cmd == "once":
+        cmd_once(a)
     elif a.cmd == "generic":
         if a.table_only:
             write_generic(a.db, a.out)
