@@ -1013,6 +1013,11 @@ def rows_per_tile(v):
     return 64 * c["U"] * c["WPB"] if c["kind"] == "valu" else 16 * c["U"] * c["WPB"]
 
 
+def sums_blocks(v):
+    """Whether the kernel can sum over its blocks itself."""
+    return int(v["op"] == "tsmttsm" and v["cfg"]["kind"] in ("packed", "valu"))
+
+
 def _launcher(v, fn):
     tmpl = _template(v)
     threads = 64 * v["cfg"]["WPB"]
@@ -1036,6 +1041,8 @@ def _launcher(v, fn):
                 % (fn, tmpl, threads, fn.replace("launch_", "kernel_"), tmpl))
     if v["op"] == "tsmttsm":
         args = "p.K, p.M, p.N, p.A, p.lda, p.X, p.ldx, static_cast<double*>(p.Y), p.ldy, p.ws, p.conj"
+        if sums_blocks(v):
+            args += ", p.arrived"
     else:
         args = ("p.K, p.M, p.N, p.A, p.lda, static_cast<const double*>(p.X), p.ldx, p.Y, p.ldy, "
                 "p.alpha, p.beta, p.conj, p.opc")
@@ -1057,14 +1064,14 @@ def _record(v, fn):
     flat_a = int(bool(c.get("FL")) or c["kind"] in ("lds", "dot"))
     read_b = int(bool(c.get("RB")))
     align16 = int(c["kind"] in ("lds", "dot"))
-    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d},\n'
+    return ('    {%d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, "%s", &%s, &%s, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d, %d},\n'
             % (OPS[v["op"]], DTYPES[v["dt"]][0], v["M"], v["N"], v["maxM"], v["maxN"], pair_a, pair_x, even,
                64 * c["WPB"], rows_per_tile(v), pack, flat_a, read_b, align16, variant_name(v),
                fn.replace("launch_", "kernel_"), fn, 0 if c["kind"] != "stage" else 2 if c.get("SYM") else 1,
                c.get("NS", 0), int(c["kind"] == "stage" and bool(c.get("G3"))),
                stage_fold(v["dt"], c) if c["kind"] == "stage" else 0, 16 * c["U"] if c["kind"] == "once" else 0,
                once_c_bytes(v["dt"], c) if c["kind"] == "once" else 0, c.get("DB", 0),
-               *(once_above(v) if c["kind"] == "once" else (0, 0)), c.get("full", 1)))
+               *(once_above(v) if c["kind"] == "once" else (0, 0)), c.get("full", 1), sums_blocks(v)))
 
 
 # batched orthogonalisation: input bytes per slab and queue interleave (0: every

@@ -240,4 +240,65 @@ __device__ __forceinline__ void block_out(const double* part, int E, int N, doub
     }
 }
 
+// The same, and the sum over the blocks with it (TH threads; arrived null:
+// block_out).  The block that arrives last at the counter sums all slots,
+// each entry in the order of the slots over its threads' share of them and
+// then over the shares by a fixed tree, so the result does not depend on which
+// block that is; it leaves the counter at zero for the next launch.  Slots are
+// written through to memory, counted once they are there and read past the
+// caches, so that no cache is flushed or invalidated.
+//
+// Worth it where the slots are few: one compute unit reads them, but a launch
+// is saved, which is most of a small call.
+template <int CW, int TH>
+__device__ __forceinline__ void block_sum(const double* part, int E, int N, double* __restrict__ ws,
+                                          double* __restrict__ C, int64_t ldc, unsigned* arrived, double* red)
+{
+    if (!arrived) {
+        block_out<CW>(part, E, N, ws, C, ldc);
+        return;
+    }
+    const int G = gridDim.x;
+    double* dst = ws + (size_t)blockIdx.x * E;
+    for (int e = threadIdx.x; e < E; e += TH)
+        __hip_atomic_store(dst + e, part[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    __shared__ int last;
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(G - 1);
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    int EB = 1;
+    while (EB < E && EB < TH) EB <<= 1;
+    const int S = TH / EB, el = threadIdx.x & (EB - 1), s = threadIdx.x / EB;
+    for (int e0 = 0; e0 < E; e0 += EB) {
+        const int e = e0 + el;
+        double v = 0.0;
+        if (e < E)
+            for (int b = s; b < G; b += 8 * S) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    x[u] = __hip_atomic_load(ws + (size_t)min(b + u * S, G - 1) * E + e, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v += b + u * S < G ? x[u] : 0.0;
+            }
+        red[threadIdx.x] = v;
+        __syncthreads();
+        for (int h = S / 2; h >= 1; h >>= 1) {
+            if (s < h) red[threadIdx.x] += red[threadIdx.x + h * EB];
+            __syncthreads();
+        }
+        if (s == 0 && e < E) {
+            const int q = e / CW;
+            const int m = q / N, n = q - m * N;
+            C[((int64_t)m * ldc + n) * CW + (e - q * CW)] = red[el];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 }  // namespace tsg

@@ -556,7 +556,7 @@ template <int MC, int NC, int U, bool CPLX, int WPB, int NBUF, bool F32 = false>
 __global__ void __launch_bounds__(WPB * kWave)
 tsmttsm_packed(int64_t K, int Mr, int Nr, const void* __restrict__ Av, int64_t lda,
                const void* __restrict__ Bv, int64_t ldb, double* __restrict__ C, int64_t ldc,
-               double* __restrict__ ws, int conj)
+               double* __restrict__ ws, int conj, unsigned* arrived)
 {
     using T = elem_t<CPLX>;
     using S = typename storage<CPLX, F32>::type;  // storage type; loads widen S -> T
@@ -637,7 +637,7 @@ tsmttsm_packed(int64_t K, int Mr, int Nr, const void* __restrict__ Av, int64_t l
         fin[e] = s;
     }
     __syncthreads();
-    block_out<CW>(fin, E, N, ws, C, ldc);
+    block_sum<CW, WPB * kWave>(fin, E, N, ws, C, ldc, arrived, part);
 }
 
 // ============================================================================
@@ -661,7 +661,7 @@ template <int MC, int NC, int MX, int NX, int U, bool CPLX, bool VA, bool VB, in
 __global__ void __launch_bounds__(WPB * kWave)
 tsmttsm_valu(int64_t K, int Mr, int Nr, const void* __restrict__ Av, int64_t lda,
              const void* __restrict__ Bv, int64_t ldb, double* __restrict__ C, int64_t ldc,
-             double* __restrict__ ws, int conj)
+             double* __restrict__ ws, int conj, unsigned* arrived)
 {
     using T = elem_t<CPLX>;
     constexpr int CW = CPLX ? 2 : 1;
@@ -783,7 +783,8 @@ tsmttsm_valu(int64_t K, int Mr, int Nr, const void* __restrict__ Av, int64_t lda
         }
         __syncthreads();
     }
-    block_out<CW>(part, E, N, ws, C, ldc);
+    __shared__ double red[WPB * kWave];
+    block_sum<CW, WPB * kWave>(part, E, N, ws, C, ldc, arrived, red);
 }
 
 // ============================================================================

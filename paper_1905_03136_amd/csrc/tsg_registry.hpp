@@ -25,6 +25,7 @@ struct Launch {
     double alpha, beta;
     double* ws;  // TSMTTSM: one slot of M*N (x2 complex) doubles per block
     size_t lds;  // bytes of LDS of a block, for kernels that size it at run time
+    unsigned* arrived;  // TSMTTSM: counter of the blocks, zero (null: the slots are summed by another kernel)
 };
 
 enum OpKind { OP_TSMTTSM = 0, OP_TSMM = 1 };
@@ -61,6 +62,7 @@ struct Variant {
     int once_db;  // two tiles of a wave in LDS, persistent blocks
     int once_m, once_n;  // it serves widths above these: those of the next smaller class
     int once_full;       // and its largest widths (0: another kernel is faster at just those)
+    int sums;  // TSMTTSM: takes Launch.arrived
 };
 
 // LDS bytes of a block of the staged kernel: NS stages of RT rows of both

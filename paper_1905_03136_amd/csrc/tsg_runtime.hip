@@ -97,6 +97,13 @@ __global__ void __launch_bounds__(256) clear_small(double* __restrict__ C, int M
 // device address obtained once per device with hipGetSymbolAddress.
 constexpr size_t kScratchBytes = size_t(32) << 20;
 static __device__ __align__(256) double scratch[kScratchBytes / sizeof(double)];
+// The no-alloc calls' counter of arrived blocks, zero between launches.
+static __device__ unsigned scratch_count;
+
+__global__ void clear_counter(unsigned* c)
+{
+    if (threadIdx.x == 0) *c = 0u;
+}
 
 }  // namespace tsg
 
@@ -141,7 +148,7 @@ struct DeviceInfo {
 };
 
 struct Workspace {
-    void* data = nullptr;
+    void* data = nullptr;  // `bytes` of it, and a counter (zero between launches)
     size_t bytes = 0;
 };
 
@@ -154,7 +161,7 @@ std::vector<std::pair<int, void*>> g_retired;
 // (device, variant, LDS bytes of a block) -> blocks per CU
 std::map<std::tuple<int, const tsg::Variant*, size_t>, int> g_occ;
 
-std::map<int, double*> g_scratch;  // device -> device address of its no-alloc scratch
+std::map<int, std::pair<double*, unsigned*>> g_scratch;  // device -> addresses of its no-alloc scratch and counter
 
 int is_complex(tsg_dtype dt) { return dt == TSG_C128 || dt == TSG_C64 || dt == TSG_C64_ACC32; }
 size_t elem_bytes(tsg_dtype dt)
@@ -220,20 +227,23 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 // Device address of `dev`'s scratch array; `dev` must be the current device.
 // Resolved on the first use per device (tsg_init or the first no-alloc call).
-tsg_status scratch_of(int dev, double** out)
+tsg_status scratch_of(int dev, double** out, unsigned** count)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_scratch.find(dev);
     if (it != g_scratch.end()) {
-        *out = it->second;
+        *out = it->second.first;
+        *count = it->second.second;
         return TSG_OK;
     }
-    void* p = nullptr;
+    void *p = nullptr, *c = nullptr;
     hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(tsg::scratch));
-    if (e != hipSuccess || !p)
+    if (e == hipSuccess) e = hipGetSymbolAddress(&c, HIP_SYMBOL(tsg::scratch_count));
+    if (e != hipSuccess || !p || !c)
         return fail(TSG_E_HIP, "hipGetSymbolAddress(scratch) on device %d: %s", dev, hipGetErrorString(e));
-    g_scratch[dev] = static_cast<double*>(p);
+    g_scratch[dev] = std::make_pair(static_cast<double*>(p), static_cast<unsigned*>(c));
     *out = static_cast<double*>(p);
+    *count = static_cast<unsigned*>(c);
     return TSG_OK;
 }
 
@@ -412,8 +422,14 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace** 
     // the outgrown buffer is retired, not freed (see g_retired)
     const size_t grow = bytes < (1u << 20) ? (1u << 20) : bytes;
     void* fresh = nullptr;
-    e = hipMalloc(&fresh, grow);
-    if (e != hipSuccess) return fail(TSG_E_NOMEM, "hipMalloc(%zu): %s", grow, hipGetErrorString(e));
+    e = hipMalloc(&fresh, grow + 256);
+    if (e != hipSuccess) return fail(TSG_E_NOMEM, "hipMalloc(%zu): %s", grow + 256, hipGetErrorString(e));
+    hipLaunchKernelGGL(tsg::clear_counter, dim3(1), dim3(64), 0, stream,
+                       reinterpret_cast<unsigned*>(static_cast<char*>(fresh) + grow));
+    if ((e = hipGetLastError()) != hipSuccess) {
+        hipFree(fresh);
+        return fail(TSG_E_HIP, "clearing a workspace's counter: %s", hipGetErrorString(e));
+    }
     if (w.data) g_retired.emplace_back(dev, w.data);
     w.data = fresh;
     w.bytes = grow;
@@ -509,6 +525,24 @@ hipError_t launch_fold(const tsg::Launch& p, bool cplx)
     return hipGetLastError();
 }
 
+// Whether the kernel sums over its blocks itself (block_sum) instead of
+// leaving it to fold_partials: few blocks with few partial sums, where the
+// launch saved is more than one compute unit's reading of them.  Calls in a
+// row, two launches -> one: 10007 x 4 and 4 (20 blocks, 3 KB) 6.0 -> 4.6 us,
+// complex 8 and 8 (40 blocks, 40 KB) 6.6 -> 6.2; on the other side 40000 x 8
+// and 8 (79 blocks, 40 KB) 6.35 and 6.40, 10007 x 16 and 4 (157 blocks, 80 KB)
+// 7.1 and 8.1, 200000 x 2 and 2 (196 blocks, 6 KB) 5.8 and 6.6.  The handle of
+// the per-thread streams stands for several streams, which share a workspace
+// and so a counter: not there.
+constexpr int kSelfSumBlocks = 64;
+constexpr size_t kSelfSumBytes = 40960;
+
+bool sums_itself(const tsg::Variant& v, int grid, size_t bytes, hipStream_t stream)
+{
+    return v.sums && grid > 1 && grid <= kSelfSumBlocks && bytes <= kSelfSumBytes &&
+           g_reduction == TSG_REDUCE_FOLD && stream != hipStreamPerThread;
+}
+
 // TSMTTSM launch shared by tsg_tsmttsm (per-stream workspace, allocated on
 // first need) and tsg_tsmttsm_noalloc (the device's fixed scratch array).
 tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N, const void* A, int64_t lda,
@@ -539,20 +573,25 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
     p.Y = C;
     p.ldy = ldc;
     const size_t need = tsmttsm_ws_bytes(p.grid, M, N, is_complex(dt));
+    const bool self_sum = sums_itself(*v, p.grid, need, p.stream);
     if (noalloc) {
         if (need > tsg::kScratchBytes)
             return fail(TSG_E_UNSUPPORTED, "TSMTTSM %dx%d on %d blocks needs %zu bytes of partial sums, more than "
                         "the %zu bytes of the no-alloc scratch", M, N, p.grid, need, tsg::kScratchBytes);
-        if ((s = scratch_of(dev, &p.ws)) != TSG_OK) return s;
+        unsigned* count = nullptr;
+        if ((s = scratch_of(dev, &p.ws, &count)) != TSG_OK) return s;
+        if (self_sum) p.arrived = count;
     } else {
         Workspace* w = nullptr;
         if ((s = get_workspace(dev, p.stream, need, &w)) != TSG_OK) return s;
         p.ws = static_cast<double*>(w->data);
+        if (self_sum) p.arrived = reinterpret_cast<unsigned*>(static_cast<char*>(w->data) + w->bytes);
     }
     p.lds = lds_for(*v, M, N);
     v->launch(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));
+    if (p.arrived) return TSG_OK;
     if (p.grid > 1 && g_reduction == TSG_REDUCE_ATOMIC) {
         const int cw = is_complex(dt) ? 2 : 1;
         const int E = M * N * cw;
@@ -704,7 +743,8 @@ tsg_status tsg_init(int32_t device)
     if (cur != device && (e = hipSetDevice(device)) != hipSuccess)
         return fail(TSG_E_HIP, "hipSetDevice(%d): %s", device, hipGetErrorString(e));
     double* ws = nullptr;
-    s = scratch_of(device, &ws);
+    unsigned* count = nullptr;
+    s = scratch_of(device, &ws, &count);
     if (cur != device) hipSetDevice(cur);
     return s;
 }
