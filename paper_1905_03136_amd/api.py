@@ -1,13 +1,27 @@
 """torch-facing entry points.  torch supplies device memory and streams only;
 the arithmetic runs in libtsgemm's HIP kernels (see ``_lib``)."""
+import ctypes
+
 import torch
 
 from . import _lib
+
+try:
+    from . import _calls
+except ImportError as e:
+    raise ImportError("_calls.so is not built for this Python and torch (%s); run __graft_entry__.build() or "
+                      "python -m paper_1905_03136_amd.build" % e) from e
 
 _DT = {torch.float64: _lib.TSG_R64, torch.complex128: _lib.TSG_C128,
        torch.float32: _lib.TSG_R32, torch.complex64: _lib.TSG_C64}
 _SMALL = {torch.float64: torch.float64, torch.complex128: torch.complex128,
           torch.float32: torch.float64, torch.complex64: torch.complex128}
+
+
+def _bind():
+    """Give the native calls the library's entry points."""
+    lib = _lib.lib()
+    _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.tsg_tsmttsm, lib.tsg_tsmm_op)))
 
 
 def _ld(X, name):
@@ -49,6 +63,12 @@ def tsmttsm(A, B, op="T", out=None, acc="f64"):
     binary32 over stretches of 32 rows, binary64 beyond.  ``out`` may be an
     (M x N) row-major tensor to write into.
     """
+    done = _calls.tsmttsm(A, B, op, out, acc)
+    if done is not NotImplemented:
+        if type(done) is int:
+            _lib.check(done)
+        return done
+    _bind()
     if A.dtype != B.dtype or A.dtype not in _DT:
         raise TypeError("A and B must share one of float64, complex128, float32, complex64")
     if A.device != B.device or A.device.type != "cuda":
@@ -76,6 +96,12 @@ def tsmm(A, C, out=None, alpha=1.0, beta=0.0, conjA=False, opC="N", acc="f64"):
     Writes into ``out`` (K x N, A's dtype) when given, else into a new tensor
     (beta must then be 0).  C is float64 / complex128 for every storage type.
     """
+    done = _calls.tsmm(A, C, out, alpha, beta, conjA, opC, acc)
+    if done is not NotImplemented:
+        if type(done) is int:
+            _lib.check(done)
+        return done
+    _bind()
     if A.dtype not in _DT or C.dtype != _SMALL[A.dtype]:
         raise TypeError("unsupported dtype combination %s, %s" % (A.dtype, C.dtype))
     if A.device != C.device or A.device.type != "cuda":

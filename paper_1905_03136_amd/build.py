@@ -44,6 +44,9 @@ HEADERS = [os.path.join(CSRC, h) for h in ("tsg_device.hpp", "tsg_kernels.hpp", 
 # headers of the units that hold kernels bringing their rows straight into LDS
 STAGE_HEADERS = [os.path.join(CSRC, h) for h in ("tsg_stage.hpp", "tsg_once.hpp")]
 ABI_HEADER = os.path.join(ROOT, "include", "tsgemm.h")
+# the plain calls on torch tensors, a Python extension module
+CALLS = os.path.join(HERE, "_calls.so")
+CALLS_SRC = os.path.join(CSRC, "tsg_calls.cpp")
 TUNE_LIB = os.path.join(HERE, "libtsgemm_tune.so")
 # builds of other variant sets (the autotuner's libraries): generated sources
 # and objects under <repository>/_build/<tag>/, out of the package
@@ -180,6 +183,27 @@ def generate(widths=None, variants=None, gen_dir=GEN):
     return codegen.emit(gen_dir, variants, batched=codegen.tuned_batched(os.path.join(HERE, "tuned.json"))), variants
 
 
+def build_calls():
+    """Compile the native torch calls against the installed torch (host code
+    only; its addresses of libtsgemm's functions come from the loaded library)."""
+    import sysconfig
+
+    import torch
+    base = os.path.join(os.path.dirname(torch.__file__))
+    lib = os.path.join(base, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + os.path.join(ROOT, "include"),
+           "-I" + os.path.join(base, "include"),
+           "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
+           "-I" + sysconfig.get_paths()["include"], CALLS_SRC, "-o", CALLS + ".tmp", "-L" + lib, "-lc10",
+           "-ltorch_cpu", "-ltorch_python", "-lc10_hip"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("compiling %s failed:\n%s" % (CALLS_SRC, r.stdout[-6000:]))
+    os.replace(CALLS + ".tmp", CALLS)
+    return CALLS
+
+
 def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, lib_path=LIB, tag=""):
     """Generate and compile.  ``variants`` replaces the product's variant set
     (the autotuner builds all candidates this way into its own library,
@@ -263,6 +287,7 @@ def main(argv=None):
         from paper_1905_03136_amd import codegen
         widths = codegen.GRADED
     build(widths, a.jobs)
+    build_calls()
 
 
 if __name__ == "__main__":
