@@ -766,7 +766,10 @@ def once_candidates(dt, ms, quads):
 
 
 def once_above(v):
-    """Widths of the next smaller classes: a class serves the widths above them."""
+    """Widths above which a class serves: the next smaller classes', unless the
+    table gives others."""
+    if "above" in v["cfg"]:
+        return tuple(v["cfg"]["above"])
     m, n = v["maxM"] // 4, v["maxN"] // 4
     return 4 * max([0] + [x for x in ONCE_MS if x < m]), 4 * max([0] + [x for x in ONCE_QUADS if x < n])
 
@@ -784,7 +787,7 @@ def tuned_once(path=None):
         with open(path) as f:
             for e in json.load(f).get("once", []):
                 cfg = once_config(*(e[k] for k in ("dt", "ms", "quads", "U", "CL", "OCC", "W", "DB")))
-                out[(e["dt"], e["ms"], e["quads"])] = dict(cfg, full=e["full"])
+                out[(e["dt"], e["ms"], e["quads"])] = dict(cfg, serves=e["serves"], above=e["above"])
     return out
 
 
@@ -1071,7 +1074,7 @@ def _record(v, fn):
                c.get("NS", 0), int(c["kind"] == "stage" and bool(c.get("G3"))),
                stage_fold(v["dt"], c) if c["kind"] == "stage" else 0, 16 * c["U"] if c["kind"] == "once" else 0,
                once_c_bytes(v["dt"], c) if c["kind"] == "once" else 0, c.get("DB", 0),
-               *(once_above(v) if c["kind"] == "once" else (0, 0)), c.get("full", 1), sums_blocks(v)))
+               *(once_above(v) if c["kind"] == "once" else (0, 0)), c.get("serves", 15), sums_blocks(v)))
 
 
 # batched orthogonalisation: input bytes per slab and queue interleave (0: every

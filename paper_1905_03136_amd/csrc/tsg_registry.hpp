@@ -60,8 +60,10 @@ struct Variant {
     int once;
     int once_c;
     int once_db;  // two tiles of a wave in LDS, persistent blocks
-    int once_m, once_n;  // it serves widths above these: those of the next smaller class
-    int once_full;       // and its largest widths (0: another kernel is faster at just those)
+    int once_m, once_n;  // it serves widths above these: those of the next smaller class, or nearer
+    // the calls for which no other kernel was faster: 1 beta = 0, 2 beta = 0
+    // and its largest widths, 4 and 8 the same for beta != 0
+    int once_for;
     int sums;  // TSMTTSM: takes Launch.arrived
 };
 

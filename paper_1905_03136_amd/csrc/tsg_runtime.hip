@@ -250,18 +250,19 @@ tsg_status scratch_of(int dev, double** out, unsigned** count)
 // Choose the variant: the exact (op, dtype, M, N) one if its access
 // requirements hold, else the first run-time-width variant covering (M, N).
 const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_t lda, const void* X,
-                             int64_t ldx, bool beta_nz);
+                             int64_t ldx, bool beta_nz, int64_t K);
 
 // The variant of (op, dt): for a binary32-arithmetic type, its own exact-width
-// variant if there is one, else what its binary64-arithmetic twin would run.
+// variant if there is one, else what its binary64-arithmetic twin would run
+// (K: rows of the call, many if not given).
 const tsg::Variant* pick(int op, tsg_dtype dt, int M, int N, const void* A, int64_t lda, const void* X,
-                         int64_t ldx, bool beta_nz = false)
+                         int64_t ldx, bool beta_nz = false, int64_t K = INT64_MAX)
 {
     if (elem_bytes(dt) == 0) return nullptr;
-    const tsg::Variant* v = pick_for(op, (int)dt, M, N, A, lda, X, ldx, beta_nz);
+    const tsg::Variant* v = pick_for(op, (int)dt, M, N, A, lda, X, ldx, beta_nz, K);
     const int twin = twin_of(dt);
     if (twin >= 0 && (!v || v->M == 0)) {
-        const tsg::Variant* w = pick_for(op, twin, M, N, A, lda, X, ldx, beta_nz);
+        const tsg::Variant* w = pick_for(op, twin, M, N, A, lda, X, ldx, beta_nz, K);
         if (w) return w;
     }
     return v;
@@ -341,9 +342,25 @@ struct VariantIndex {
 // The LDS-staged kernel of a TSMTTSM, or null: widths above 16, 16-byte
 // aligned matrices of a layout it can read; a matrix with itself (a Gram
 // matrix) takes the form that reads it once and forms half of the products.
-const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb)
+const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb, int64_t K)
 {
     if (M <= 16 && N <= 16) return nullptr;
+    if (dt == TSG_C128) {
+        const int wide = M > N ? M : N, narrow = M > N ? N : M;
+        const int padded = (wide + 15) / 16 * 16 * ((narrow + 3) / 4 * 4);  // products it forms, a row
+        // few rows of wide matrices: its blocks of many row groups get one or
+        // two tiles each (58 x 16, 10007 rows: 14.4 us against 10.8, 100003 rows
+        // 32 and 29; 64 x 28, 30000 rows 1.25 of the others' time, 100003 1.00).
+        // Squares stay: 64 x 64, 30000 rows 35 us against 39
+        if (M != N && wide > 48 && narrow > 8 && K < 65536) return nullptr;
+        // bound by the matrix cores: squares whose products it pads by more than
+        // 1.6 (17 to 19 columns) have kernels of their widths (2^20 rows of 17 x
+        // 17: 0.79 of its time; 20 x 20 1.17), and 13 to 16 columns against up
+        // to 48 that do not fill their blocks are 0.89 of it from long matrices
+        // on (15 x 23, 25 x 15, 33 x 13; at 100003 rows 1.10 to 1.18)
+        if (M == N && 10 * padded > 16 * M * N) return nullptr;
+        if (narrow > 12 && narrow <= 16 && wide <= 48 && wide % 16 && K >= (1 << 19)) return nullptr;
+    }
     const bool sym = M == N && A == B && lda == ldb;
     const int gauss = !sym && stage_gauss(dt, M, N);
     for (const tsg::Variant* v : VariantIndex::get().type(tsg::OP_TSMTTSM, dt).stage)
@@ -381,7 +398,7 @@ bool once_serves(const tsg::Variant& v, int M, int N, const void* A, int64_t lda
 }
 
 const tsg::Variant* pick_once(int dt, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb,
-                              bool beta_nz)
+                              bool beta_nz, int64_t K)
 {
     // the narrow non-square pairs in binary64 have kernels of their exact
     // widths, which multiply no zeros (2^22 rows, 4 x 8: 71 us there, 69 here;
@@ -389,11 +406,21 @@ const tsg::Variant* pick_once(int dt, int M, int N, const void* A, int64_t lda, 
     if (M <= 8 && N <= 8 && M != N && (dt == TSG_R64 || dt == TSG_C128)) return nullptr;
     const tsg::Variant* v = VariantIndex::get().type(tsg::OP_TSMM, dt).once[M * VariantIndex::kW + N];
     if (!v || !once_serves(*v, M, N, A, lda, B, ldb, beta_nz)) return nullptr;
-    return v->once_full || M < v->maxM || N < v->maxN ? v : nullptr;
+    // Few rows: a wave's chain of load, multiply, exchange and store is what the
+    // call takes, and tiles of several 16 rows make it longer than in the
+    // kernels with more and smaller waves: 30000 rows, tiles of 64 in binary32
+    // 15 x 15 5.0 -> 6.7 us, 32 x 16 5.2 -> 10.0 (300000 rows 28 -> 20); tiles of
+    // 16 rows gain at any length (doubles 12 x 40, 10007 rows: 8.2 -> 4.3), but
+    // for the old rows of an update of a few (complex64 20 x 20, 10007 rows:
+    // 5.4 -> 6.5, 30000: 7.7 -> 6.0).
+    const int64_t tiles = K / v->once;
+    if (v->once > 16 ? tiles < (beta_nz && v->once > 32 ? 6144 : 4096) : beta_nz && tiles < 1024) return nullptr;
+    const int call = (M == v->maxM && N == v->maxN ? 2 : 1) * (beta_nz ? 4 : 1);
+    return v->once_for & call ? v : nullptr;
 }
 
 const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_t lda, const void* X,
-                             int64_t ldx, bool beta_nz)
+                             int64_t ldx, bool beta_nz, int64_t K)
 {
     const bool a_pairs = (lda % 2 == 0) && aligned(A, 16);
     const bool x_pairs = (ldx % 2 == 0) && aligned(X, 16);
@@ -414,18 +441,30 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
         return nullptr;
     }
     if (op == tsg::OP_TSMTTSM)
-        if (const tsg::Variant* v = pick_stage(dt, M, N, A, lda, X, ldx)) return v;
+        if (const tsg::Variant* v = pick_stage(dt, M, N, A, lda, X, ldx, K)) return v;
     if (op == tsg::OP_TSMM)
-        if (const tsg::Variant* v = pick_once(dt, M, N, A, lda, X, ldx, beta_nz)) return v;
+        if (const tsg::Variant* v = pick_once(dt, M, N, A, lda, X, ldx, beta_nz, K)) return v;
     auto can = [&](const tsg::Variant& v) {
         return (!v.pairA || a_pairs) && (!v.pairX || x_pairs) && (!v.flatA || rows_contiguous) &&
                (!v.readB || beta_nz) && (!v.align16 || ax16);
     };
     const VariantIndex::PerType& t = VariantIndex::get().type(op, dt);
+    auto covers = [&](const tsg::Variant& v) {
+        return M <= v.maxM && N <= v.maxN && (!v.evenW || (M % 2 == 0 && N % 2 == 0)) && can(v);
+    };
+    // wide complex B += A C: a kernel that reads the old B along with A, of
+    // these widths or, where their own would spill, of a range (2^20 rows,
+    // 33 x 33 625 -> 369 us, 48 x 48 728 -> 456, 16 x 40 583 -> 299)
+    if (op == tsg::OP_TSMM && beta_nz && (dt == TSG_C128 || dt == TSG_C64) && (M > 16 || N > 16)) {
+        for (const tsg::Variant* v : t.exact[M * VariantIndex::kW + N])
+            if (v->readB && can(*v)) return v;
+        for (const tsg::Variant* v : t.ranges)
+            if (v->readB && covers(*v)) return v;
+    }
     for (const tsg::Variant* v : t.exact[M * VariantIndex::kW + N])
         if (can(*v)) return v;
     for (const tsg::Variant* v : t.ranges)
-        if (M <= v->maxM && N <= v->maxN && (!v->evenW || (M % 2 == 0 && N % 2 == 0)) && can(*v)) return v;
+        if (covers(*v)) return v;
     return nullptr;
 }
 
@@ -580,7 +619,7 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
     if ((s = current_device(&dev)) != TSG_OK) return s;
     DeviceInfo di;
     if ((s = device_info(dev, &di)) != TSG_OK) return s;
-    const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, A, lda, B, ldb);
+    const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, A, lda, B, ldb, false, K);
     if (!v) return fail(TSG_E_UNSUPPORTED, "no kernel variant for TSMTTSM %dx%d%s", M, N,
                         g_force.empty() ? "" : " (a forced variant does not apply)");
     tsg::Launch p{};
@@ -670,7 +709,7 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
     if ((s = current_device(&dev)) != TSG_OK) return s;
     DeviceInfo di;
     if ((s = device_info(dev, &di)) != TSG_OK) return s;
-    const tsg::Variant* v = pick(tsg::OP_TSMM, dt, M, N, A, lda, B, ldb, beta != 0.0);
+    const tsg::Variant* v = pick(tsg::OP_TSMM, dt, M, N, A, lda, B, ldb, beta != 0.0, K);
     if (!v) return fail(TSG_E_UNSUPPORTED, "no kernel variant for TSMM %dx%d%s", M, N,
                         g_force.empty() ? "" : " (a forced variant does not apply)");
     tsg::Launch p{};
@@ -717,7 +756,7 @@ size_t tsg_workspace_size(int32_t op_kind, tsg_dtype dt, int64_t K, int32_t M, i
     alignas(16) static const char buf16[32] = {0};
     size_t need = 0;
     for (int pad = 0; pad < 2; ++pad) {
-        const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, buf16, M + pad * (M & 1), buf16 + 16, N + pad * (N & 1));
+        const tsg::Variant* v = pick(tsg::OP_TSMTTSM, dt, M, N, buf16, M + pad * (M & 1), buf16 + 16, N + pad * (N & 1), false, K);
         if (!v) continue;
         const size_t b = tsmttsm_ws_bytes(grid_for(dev, *v, K, M, N, di.cus), M, N, is_complex(dt));
         need = need > b ? need : b;

@@ -355,24 +355,80 @@ def once_tuning_variants():
             for cls in codegen.once_classes() for c in codegen.once_candidates(*cls)]
 
 
-def _other_tsmm(dt, M, N, names):
+def once_serves(dt, v, name, names):
+    """(mask, above) of a class: the calls in which its kernel is not slower than
+    the others, timed on the largest widths, one less and the smallest, for
+    beta = 0 and 1.  1: beta = 0 below the largest widths, 2: beta = 0 at
+    them, 4 and 8: beta = 1.  Where only the smallest widths are slower the
+    class serves the largest two of each side."""
+    import torch
+    from paper_1905_03136_amd import _lib, api, codegen
+    M, N = v["maxM"], v["maxN"]
+    above = list(codegen.once_above(v))
+    es = (2 if codegen.DTYPES[dt][1] else 1) * (4 if codegen.is_f32(dt) else 8)
+    tdt = {8: torch.complex64, 16: torch.complex128}[es] if codegen.DTYPES[dt][1] else {4: torch.float32, 8: torch.float64}[es]
+
+    def us(name, m, n, beta):
+        K = min(1 << 21, (1 << 30) // (es * max(m, n)))
+        A, out = (torch.randn(K, w, dtype=tdt, device="cuda:0") for w in (m, n))
+        C = torch.randn(m, n, dtype=api._SMALL[tdt], device="cuda:0") * 1e-3
+        _lib.check(_lib.tsg_force_variant(name))
+        best = []
+        try:
+            for _ in range(5):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(4):
+                    api.tsmm(A, C, out=out, beta=beta)
+                b.record()
+                b.synchronize()
+                best.append(a.elapsed_time(b))
+        except _lib.TsgError:
+            return None  # does not fit LDS with the old rows
+        finally:
+            _lib.tsg_force_variant("")
+        return min(best)
+
+    def ratio(m, n, beta):
+        own = us(name, m, n, beta)
+        return own / us(codegen.variant_name(_other_tsmm(dt, m, n, names, beta)), m, n, beta) if own else 9.9
+
+    r = {b: [ratio(*p, b) for p in ((M, N), (M - 1, N - 1), (above[0] + 1, above[1] + 1))] for b in (0.0, 1.0)}
+    return once_mask(r[0.0], r[1.0], M, N, above)
+
+
+def once_mask(zero, one, M, N, above):
+    """The decision of once_serves from the (largest, one less, smallest) ratios."""
+    if zero[1] <= 1.05 < zero[2]:
+        above = [M - 2, N - 2]
+        zero, one = zero[:2] + [zero[1]], one[:2] + [one[1]]
+    mask = 0
+    for bit, (full, odd, low) in ((1, zero), (4, one)):
+        if max(odd, low) <= 1.05:
+            mask |= bit
+        if full <= 1.01:
+            mask |= 2 * bit
+    return mask, [max(0, x) for x in above]
+
+
+def _other_tsmm(dt, M, N, names, beta=0.0):
     """The TSMM variant the library would pick without tsmm_once (contiguous
-    aligned matrices, beta = 0)."""
+    aligned matrices)."""
     from paper_1905_03136_amd import codegen
     path = os.path.join(HERE, "tuned.json")
     widths = list(dict.fromkeys(codegen.GRADED + codegen.SQUARE_ALL + codegen.NARROW))
     exact = codegen.exact_variants([(M, N)] if (M, N) in widths else [], codegen.load_tuned(path))
     for v in exact + codegen.generic_variants(path):
-        if (v["op"], v["dt"]) == ("tsmm", dt) and not v["cfg"].get("RB") and codegen.variant_name(v) in names                 and M <= v["maxM"] and N <= v["maxN"]:
+        if (v["op"], v["dt"]) == ("tsmm", dt) and (beta or not v["cfg"].get("RB")) and codegen.variant_name(v) in names                 and M <= v["maxM"] and N <= v["maxN"]:
             return v
 
 
 def cmd_once(args):
     """GPU: time the candidates of every class of tsmm_once, and the other TSMM
     kernels the library would pick, on the class's largest widths and on odd
-    ones; classes where tsmm_once is the faster (by the mean over the pairs
-    of time over the other's time, and on the odd widths) go into the table's
-    "once" list, with full = 0 where the other is the faster on the largest."""
+    ones, and take the best by the mean over the pairs of time over the
+    other's time.  Classes where that is below 0.99 go into the table's "once"
+    list with what they serve (once_serves)."""
     sys.path.insert(0, ROOT)
     from paper_1905_03136_amd import build, codegen
     os.environ.setdefault("TSG_LIBRARY", build.tagged_lib(args.tag))
@@ -399,9 +455,10 @@ def cmd_once(args):
         c = by[name][0][1]["cfg"]
         print("[tune] %-45s %.3f of %s; %s GB/s, other %s" % (
             name, score, other[0]["name"], [r["GBps"] for _, r in by[name]], [r["GBps"] for r in other]), flush=True)
-        full, odd = (r["us"] / o["us"] for (_, r), o in zip(by[name], other))
-        if score < 0.99 and odd < 1.02:
-            entries.append(dict(dt=dt, ms=ms, quads=q, U=c["U"], CL=c["CL"], OCC=c["OCC"], W=c["WPB"], DB=c["DB"], full=int(full <= 1.0),
+        v = next(v for v in vs if codegen.variant_name(v) == name)
+        serves, above = once_serves(dt, v, name, timer.names) if score < 0.99 else (0, [0, 0])
+        if serves:
+            entries.append(dict(dt=dt, ms=ms, quads=q, U=c["U"], CL=c["CL"], OCC=c["OCC"], W=c["WPB"], DB=c["DB"], serves=serves, above=above,
                                 score=round(score, 4), other=other[0]["name"]))
     tab = {"entries": []}
     if os.path.exists(args.out):

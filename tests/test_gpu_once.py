@@ -98,3 +98,18 @@ def test_a_bad_row_stays_in_its_row(M, N, bad):
     clean[[0, 37, 512, 1023]] = False
     assert np.array_equal(got[clean], A[clean] @ X)
     assert not np.isfinite(got[~clean]).all(axis=1).any()
+
+
+@pytest.mark.parametrize("dt", ["c128", "c64"])
+@pytest.mark.parametrize("M,N", [(17, 17), (33, 33), (16, 40), (46, 46), (48, 48), (64, 64), (40, 64)])
+def test_wide_complex_updates(dt, M, N):
+    """Wide complex updates take a kernel that reads the old values with A, of
+    their own widths or of a range."""
+    for K in (1, 130, 4111):
+        print("update %s %dx%d K=%d" % (dt, M, N, K), flush=True)
+        A = inputs.host_integers(K, M, 95, inputs.STREAM_A, True)
+        X = inputs.host_integers(M, N, 95, inputs.STREAM_C, True)
+        old = inputs.host_integers(K, N, 95, inputs.STREAM_B, True)
+        for la, lb in (((0, 0), (0, 0)), ((3, 0), (2, 0)), ((0, 1), (1, 1))):
+            check(A, X, old, dt, la, lb, alpha=-1.0, beta=1.0)
+            check(A, X, old, dt, la, lb, beta=2.0, conjA=True, opC="C")
