@@ -745,10 +745,12 @@ def once_candidates(dt, ms, quads):
             creg = 0 if cl else ms * groups * cw
             if creg > 24 or (cl and ms * groups * cw < 4):
                 continue
-            for occ in (2, 4):
-                # registers in binary64 units: accumulators, C, operands, addresses
+            for occ in (2, 3, 4):
+                # registers in binary64 units: accumulators, C, operands,
+                # addresses (with few waves asked for, the compiler reads more of C
+                # ahead: doubles 32 x 32 5.65 TB/s at 4, 6.04 at 2)
                 regs = acc + creg + 2 * cw * u + 12
-                if regs > (120 if occ == 2 else 60) or (occ == 2 and regs <= 44):
+                if regs > {2: 120, 3: 80, 4: 60}[occ] or (occ < 4 and regs <= 44 and ms * quads * cw < 24):
                     continue
                 for w in (4, 8, 16) if cl else (4,):
                     c = once_config(dt, ms, quads, u, cl, occ, w)

@@ -28,7 +28,9 @@
 // -> 5501; binary32 storage 24 x 16 2630 -> 4972, 48 x 48 2111 -> 4034 (DB);
 // complex of it 20 x 20 2409 -> 3848, 40 x 24 2123 -> 3425 (DB).  Where C
 // outgrows this form tsmm_mfma's persistent waves with operands in registers
-// stay ahead: binary64 48 x 48 614 us against 655 here, complex 48 x 48 1413
+// stay ahead (32 x 32 is the last binary64 square: 2^21 rows 196 us there, 190
+// here with registers for four waves a SIMD, 178 for two, which lets more of C
+// be read ahead of the products): binary64 48 x 48 614 us against 655 here, complex 48 x 48 1413
 // against more than 1600, complex 64 x 64 2108 against 4444.
 #pragma once
 #include "tsg_stage.hpp"
