@@ -407,8 +407,9 @@ tsg_status tsg_set_grid_limit(int32_t blocks);
 /* Ablation of the cross-block reduction of TSMTTSM (the paper's Section 3.2
  * and 5.5 compare reduction variants against K).  Affects the calling
  * thread's following TSMTTSM calls whose grid has more than one block:
- *   TSG_REDUCE_FOLD    the default: per-block partials summed by a second
- *                      kernel in a fixed order (bitwise reproducible);
+ *   TSG_REDUCE_FOLD    the default: per-block partials summed in a fixed order
+ *                      (bitwise reproducible), by a second kernel or, for few
+ *                      blocks, by the last of them in the same launch;
  *   TSG_REDUCE_ATOMIC  every block's partial added into C with global FP64
  *                      atomics (C cleared first); the order of the additions
  *                      and so the rounding varies from run to run;
