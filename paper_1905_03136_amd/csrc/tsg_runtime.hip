@@ -97,8 +97,6 @@ __global__ void __launch_bounds__(256) clear_small(double* __restrict__ C, int M
 // device address obtained once per device with hipGetSymbolAddress.
 constexpr size_t kScratchBytes = size_t(32) << 20;
 static __device__ __align__(256) double scratch[kScratchBytes / sizeof(double)];
-// The no-alloc calls' counter of arrived blocks, zero between launches.
-static __device__ unsigned scratch_count;
 
 __global__ void clear_counter(unsigned* c)
 {
@@ -161,7 +159,7 @@ std::vector<std::pair<int, void*>> g_retired;
 // (device, variant, LDS bytes of a block) -> blocks per CU
 std::map<std::tuple<int, const tsg::Variant*, size_t>, int> g_occ;
 
-std::map<int, std::pair<double*, unsigned*>> g_scratch;  // device -> addresses of its no-alloc scratch and counter
+std::map<int, double*> g_scratch;  // device -> device address of its no-alloc scratch
 
 int is_complex(tsg_dtype dt) { return dt == TSG_C128 || dt == TSG_C64 || dt == TSG_C64_ACC32; }
 size_t elem_bytes(tsg_dtype dt)
@@ -227,23 +225,20 @@ bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 // Device address of `dev`'s scratch array; `dev` must be the current device.
 // Resolved on the first use per device (tsg_init or the first no-alloc call).
-tsg_status scratch_of(int dev, double** out, unsigned** count)
+tsg_status scratch_of(int dev, double** out)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_scratch.find(dev);
     if (it != g_scratch.end()) {
-        *out = it->second.first;
-        *count = it->second.second;
+        *out = it->second;
         return TSG_OK;
     }
-    void *p = nullptr, *c = nullptr;
+    void* p = nullptr;
     hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(tsg::scratch));
-    if (e == hipSuccess) e = hipGetSymbolAddress(&c, HIP_SYMBOL(tsg::scratch_count));
-    if (e != hipSuccess || !p || !c)
+    if (e != hipSuccess || !p)
         return fail(TSG_E_HIP, "hipGetSymbolAddress(scratch) on device %d: %s", dev, hipGetErrorString(e));
-    g_scratch[dev] = std::make_pair(static_cast<double*>(p), static_cast<unsigned*>(c));
+    g_scratch[dev] = static_cast<double*>(p);
     *out = static_cast<double*>(p);
-    *count = static_cast<unsigned*>(c);
     return TSG_OK;
 }
 
@@ -594,16 +589,22 @@ hipError_t launch_fold(const tsg::Launch& p, bool cplx)
 // row, two launches -> one: 10007 x 4 and 4 (20 blocks, 3 KB) 6.0 -> 4.6 us,
 // complex 8 and 8 (40 blocks, 40 KB) 6.6 -> 6.2; on the other side 40000 x 8
 // and 8 (79 blocks, 40 KB) 6.35 and 6.40, 10007 x 16 and 4 (157 blocks, 80 KB)
-// 7.1 and 8.1, 200000 x 2 and 2 (196 blocks, 6 KB) 5.8 and 6.6.  The handle of
-// the per-thread streams stands for several streams, which share a workspace
-// and so a counter: not there.
+// 7.1 and 8.1, 200000 x 2 and 2 (196 blocks, 6 KB) 5.8 and 6.6.
+//
+// Launches that count together must not overlap, not even by mistake: a count
+// left over would spoil every later one.  So only where the stream orders
+// them: not in a graph (replayed anywhere), not in the no-alloc calls (one
+// scratch for all streams), not on the handle of the per-thread streams.
 constexpr int kSelfSumBlocks = 64;
 constexpr size_t kSelfSumBytes = 40960;
 
 bool sums_itself(const tsg::Variant& v, int grid, size_t bytes, hipStream_t stream)
 {
-    return v.sums && grid > 1 && grid <= kSelfSumBlocks && bytes <= kSelfSumBytes &&
-           g_reduction == TSG_REDUCE_FOLD && stream != hipStreamPerThread;
+    if (!v.sums || grid <= 1 || grid > kSelfSumBlocks || bytes > kSelfSumBytes || g_reduction != TSG_REDUCE_FOLD ||
+        stream == hipStreamPerThread)
+        return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return stream == nullptr || (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone);
 }
 
 // TSMTTSM launch shared by tsg_tsmttsm (per-stream workspace, allocated on
@@ -636,19 +637,16 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
     p.Y = C;
     p.ldy = ldc;
     const size_t need = tsmttsm_ws_bytes(p.grid, M, N, is_complex(dt));
-    const bool self_sum = sums_itself(*v, p.grid, need, p.stream);
     if (noalloc) {
         if (need > tsg::kScratchBytes)
             return fail(TSG_E_UNSUPPORTED, "TSMTTSM %dx%d on %d blocks needs %zu bytes of partial sums, more than "
                         "the %zu bytes of the no-alloc scratch", M, N, p.grid, need, tsg::kScratchBytes);
-        unsigned* count = nullptr;
-        if ((s = scratch_of(dev, &p.ws, &count)) != TSG_OK) return s;
-        if (self_sum) p.arrived = count;
+        if ((s = scratch_of(dev, &p.ws)) != TSG_OK) return s;
     } else {
         Workspace* w = nullptr;
         if ((s = get_workspace(dev, p.stream, need, &w)) != TSG_OK) return s;
         p.ws = static_cast<double*>(w->data);
-        if (self_sum) p.arrived = reinterpret_cast<unsigned*>(static_cast<char*>(w->data) + w->bytes);
+        if (sums_itself(*v, p.grid, need, p.stream)) p.arrived = reinterpret_cast<unsigned*>(static_cast<char*>(w->data) + w->bytes);
     }
     p.lds = lds_for(*v, M, N);
     v->launch(p);
@@ -806,8 +804,7 @@ tsg_status tsg_init(int32_t device)
     if (cur != device && (e = hipSetDevice(device)) != hipSuccess)
         return fail(TSG_E_HIP, "hipSetDevice(%d): %s", device, hipGetErrorString(e));
     double* ws = nullptr;
-    unsigned* count = nullptr;
-    s = scratch_of(device, &ws, &count);
+    s = scratch_of(device, &ws);
     if (cur != device) hipSetDevice(cur);
     return s;
 }
