@@ -211,7 +211,9 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
  * order, the last such group of an instance sums the groups in order into
  * C_i and marks it ready; an update item starts once its instance is ready.
  * Every item an update waits for precedes it in the queue and never waits
- * itself, so the launch cannot deadlock.  Results are deterministic: the
+ * itself, and only running blocks hold items, so the launch cannot deadlock,
+ * also where other work (another batch on another stream) keeps some of its
+ * blocks waiting for compute units.  Results are deterministic: the
  * slab boundaries and every summation order are fixed by the queue, not by
  * which block takes which item.  C_i is computed in binary64 by matrix-core
  * products of four rows, summed over the slab's rows, then over slabs in

@@ -14,12 +14,17 @@
 //    -C_i on chip and updates its rows of W_i.
 // Every phase-1 item precedes every phase-2 item in the queue and phase-1
 // items never wait, so whatever an update waits for has already been taken by
-// a running block: the waits cannot deadlock, whatever the grid.  They are
-// bounded anyway (a spin limit raises an error word instead of hanging).
-// A block starts with the item of its own number and draws its next item
-// while it works on the current one; the earliest unfinished item is then
-// still some block's current one, or comes after such an item of its block,
-// so the argument stands.
+// a running block: the waits cannot deadlock, whatever the grid and however
+// few of its blocks are resident.  They are bounded anyway (a spin limit
+// raises an error word instead of hanging).
+// A block draws every item from the queue head, the first one too, so that
+// only running blocks hold items (a first item bound to a block's number
+// would wait for a block that other launches or a mask of compute units keep
+// out, while the blocks it waits for spin on it).  It draws its next item
+// while it works on the current one: of the earliest unfinished item's block,
+// what was drawn before it is finished, so it is that block's current one and
+// waits for nothing.  (16 instances of 57 MB in all: 81 us a launch, 75 with
+// first items by number, the 512 draws of the start.)
 //
 // What blocks exchange (partial sums, group sums, C_i, the flags) goes
 // through agent-scope atomic stores and loads, which pass the XCDs' caches;
@@ -673,12 +678,17 @@ orth_persistent(const DevDesc* __restrict__ descs, const Item* __restrict__ item
     const int tid = threadIdx.x;
     // written by the set-up kernel earlier on the stream (0 when it rejected the batch)
     const int total = (int)__builtin_amdgcn_readfirstlane(ctrl->total);
-    int q = blockIdx.x;
+    auto draw = [&]() -> int {
+        return (int)__hip_atomic_fetch_add(&ctrl->head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (tid == 0) s_q = draw();
+    __syncthreads();
+    int q = __builtin_amdgcn_readfirstlane(s_q);
+    __syncthreads();
     while (q < total) {
         // the next item, drawn while this one is worked on
         int next = 0;
-        if (tid == 0)
-            next = (int)(gridDim.x + __hip_atomic_fetch_add(&ctrl->head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (tid == 0) next = draw();
         const Item it = items[q];
         const DevDesc d = descs[it.inst];
         if (it.phase == 1) {
