@@ -148,6 +148,8 @@ struct DeviceInfo {
 struct Workspace {
     void* data = nullptr;  // `bytes` of it, and a counter (zero between launches)
     size_t bytes = 0;
+    double* slots() const { return static_cast<double*>(data); }
+    unsigned* counter() const { return reinterpret_cast<unsigned*>(static_cast<char*>(data) + bytes); }
 };
 
 std::mutex g_mu;
@@ -463,7 +465,9 @@ const tsg::Variant* pick_for(int op, int dt, int M, int N, const void* A, int64_
     return nullptr;
 }
 
-tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace** out)
+// The workspace of (dev, stream), `bytes` of it at least, as it is now: another
+// thread may grow it at any time, and an outgrown one stays valid.
+tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace* out)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     const char* lim = getenv("TSG_MAX_WORKSPACE");
@@ -471,7 +475,7 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace** 
         return fail(TSG_E_NOMEM, "workspace of %zu bytes exceeds TSG_MAX_WORKSPACE=%s", bytes, lim);
     Workspace& w = g_ws[std::make_pair(dev, stream)];
     if (w.data && w.bytes >= bytes) {
-        *out = &w;
+        *out = w;
         return TSG_OK;
     }
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -481,19 +485,17 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace** 
     hipError_t e;
     // the outgrown buffer is retired, not freed (see g_retired)
     const size_t grow = bytes < (1u << 20) ? (1u << 20) : bytes;
-    void* fresh = nullptr;
-    e = hipMalloc(&fresh, grow + 256);
+    Workspace fresh;
+    fresh.bytes = grow;
+    e = hipMalloc(&fresh.data, grow + 256);
     if (e != hipSuccess) return fail(TSG_E_NOMEM, "hipMalloc(%zu): %s", grow + 256, hipGetErrorString(e));
-    hipLaunchKernelGGL(tsg::clear_counter, dim3(1), dim3(64), 0, stream,
-                       reinterpret_cast<unsigned*>(static_cast<char*>(fresh) + grow));
+    hipLaunchKernelGGL(tsg::clear_counter, dim3(1), dim3(64), 0, stream, fresh.counter());
     if ((e = hipGetLastError()) != hipSuccess) {
-        hipFree(fresh);
+        hipFree(fresh.data);
         return fail(TSG_E_HIP, "clearing a workspace's counter: %s", hipGetErrorString(e));
     }
     if (w.data) g_retired.emplace_back(dev, w.data);
-    w.data = fresh;
-    w.bytes = grow;
-    *out = &w;
+    *out = w = fresh;
     return TSG_OK;
 }
 
@@ -643,10 +645,10 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
                         "the %zu bytes of the no-alloc scratch", M, N, p.grid, need, tsg::kScratchBytes);
         if ((s = scratch_of(dev, &p.ws)) != TSG_OK) return s;
     } else {
-        Workspace* w = nullptr;
+        Workspace w;
         if ((s = get_workspace(dev, p.stream, need, &w)) != TSG_OK) return s;
-        p.ws = static_cast<double*>(w->data);
-        if (sums_itself(*v, p.grid, need, p.stream)) p.arrived = reinterpret_cast<unsigned*>(static_cast<char*>(w->data) + w->bytes);
+        p.ws = w.slots();
+        if (sums_itself(*v, p.grid, need, p.stream)) p.arrived = w.counter();
     }
     p.lds = lds_for(*v, M, N);
     v->launch(p);
@@ -784,7 +786,7 @@ tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stre
         size_t b = tsmttsm_ws_bytes(grid_for(dev, v, K, M, N, di.cus), M, N, is_complex(dt));
         if (b > need) need = b;
     }
-    Workspace* w;
+    Workspace w;
     return get_workspace(dev, static_cast<hipStream_t>(stream), need, &w);
 }
 
