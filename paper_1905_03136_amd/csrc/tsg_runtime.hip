@@ -148,6 +148,8 @@ struct DeviceInfo {
 struct Workspace {
     void* data = nullptr;  // `bytes` of it, and a counter (zero between launches)
     size_t bytes = 0;
+    std::mutex* calls = nullptr;  // held while a call's launches are enqueued: another thread's on the same stream
+                                  // would write its slots between a kernel and the sum of its slots
     double* slots() const { return static_cast<double*>(data); }
     unsigned* counter() const { return reinterpret_cast<unsigned*>(static_cast<char*>(data) + bytes); }
 };
@@ -155,6 +157,7 @@ struct Workspace {
 std::mutex g_mu;
 std::map<int, DeviceInfo> g_dev;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
+std::map<std::pair<int, hipStream_t>, std::mutex> g_ws_calls;  // never erased: calls hold pointers to them
 // Outgrown workspaces, kept until tsg_finalize: a graph captured earlier on
 // the stream may still hold one of them and write its partial sums there.
 std::vector<std::pair<int, void*>> g_retired;
@@ -473,7 +476,8 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace* o
     const char* lim = getenv("TSG_MAX_WORKSPACE");
     if (lim && bytes > (size_t)strtoull(lim, nullptr, 10))
         return fail(TSG_E_NOMEM, "workspace of %zu bytes exceeds TSG_MAX_WORKSPACE=%s", bytes, lim);
-    Workspace& w = g_ws[std::make_pair(dev, stream)];
+    const auto key = std::make_pair(dev, stream);
+    Workspace& w = g_ws[key];
     if (w.data && w.bytes >= bytes) {
         *out = w;
         return TSG_OK;
@@ -487,6 +491,7 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace* o
     const size_t grow = bytes < (1u << 20) ? (1u << 20) : bytes;
     Workspace fresh;
     fresh.bytes = grow;
+    fresh.calls = &g_ws_calls[key];
     e = hipMalloc(&fresh.data, grow + 256);
     if (e != hipSuccess) return fail(TSG_E_NOMEM, "hipMalloc(%zu): %s", grow + 256, hipGetErrorString(e));
     hipLaunchKernelGGL(tsg::clear_counter, dim3(1), dim3(64), 0, stream, fresh.counter());
@@ -639,6 +644,7 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
     p.Y = C;
     p.ldy = ldc;
     const size_t need = tsmttsm_ws_bytes(p.grid, M, N, is_complex(dt));
+    std::unique_lock<std::mutex> calls;
     if (noalloc) {
         if (need > tsg::kScratchBytes)
             return fail(TSG_E_UNSUPPORTED, "TSMTTSM %dx%d on %d blocks needs %zu bytes of partial sums, more than "
@@ -649,6 +655,7 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
         if ((s = get_workspace(dev, p.stream, need, &w)) != TSG_OK) return s;
         p.ws = w.slots();
         if (sums_itself(*v, p.grid, need, p.stream)) p.arrived = w.counter();
+        calls = std::unique_lock<std::mutex>(*w.calls);
     }
     p.lds = lds_for(*v, M, N);
     v->launch(p);

@@ -20,3 +20,23 @@ def test_slots_and_counter_of_a_call_lie_in_one_workspace(tmp_path):
         ws, arrived = kernels[0].args[9], kernels[0].args[11]
         assert arrived == ws + rec.rec_buffer(ws) - 256, (hex(ws), hex(arrived))
     ''')
+
+
+def test_calls_of_two_threads_on_one_stream_do_not_mix(tmp_path):
+    """They share the stream's workspace: between a call's kernel and the sum of
+    its slots no other call may be enqueued."""
+    run(tmp_path, '''
+        shape = (0, 0, 1000000, 8, 8, A, 8, B, 8)
+        assert lib.tsg_tsmttsm(*shape, C, 8, S) == 0
+        launches()
+        def other():
+            global t
+            t = threading.Thread(target=lambda: lib.tsg_tsmttsm(*shape, C + 4096, 8, S))
+            t.start()
+            t.join(0.5)   # enough to enqueue its launches, if nothing keeps it
+        on("launch", other)
+        assert lib.tsg_tsmttsm(*shape, C, 8, S) == 0
+        t.join()
+        names = [r.name for r in launches()]
+        assert [b"fold" in n for n in names] == [False, True, False, True], names
+    ''')
