@@ -551,10 +551,11 @@ int grid_for(int dev, const tsg::Variant& v, int64_t K, int M, int N, int cus, b
     if (v.pack == 1) rows *= 16 / (M > N ? M : N);
     if (v.pack == 2) rows *= 16 / N;
     const int64_t tiles = (K + rows - 1) / rows;
-    // the one-tile kernel of TSMM: a block for every tile
+    // the one-tile kernel of TSMM: a block for every tile, as many as a launch
+    // may have (fewer than 2^32 work items); its blocks stride over the rest
     const size_t lds = lds_for(v, M, N, beta_nz);
     const int blocks = v.once && !v.once_db && lds <= (64u << 10) ? 0 : occupancy(dev, v, lds);
-    const int64_t cap = v.once && !v.once_db ? (int64_t)1 << 30 : (int64_t)cus * blocks;
+    const int64_t cap = v.once && !v.once_db ? (((int64_t)1 << 32) - 1) / v.threads : (int64_t)cus * blocks;
     int64_t g = tiles < cap ? tiles : cap;
     if (v.op == tsg::OP_TSMTTSM) {
         // the per-block partial sums of a launch always fit the no-alloc

@@ -40,3 +40,26 @@ def test_calls_of_two_threads_on_one_stream_do_not_mix(tmp_path):
         names = [r.name for r in launches()]
         assert [b"fold" in n for n in names] == [False, True, False, True], names
     ''')
+
+
+def test_launch_sizes_of_long_matrices(tmp_path):
+    """A block for every tile as far as a launch goes (fewer than 2^32 work
+    items); beyond, fewer blocks, which stride over the tiles."""
+    out = run(tmp_path, '''
+        name = lambda dt, M, N: lib.tsg_kernel_name(1, dt, 0, M, N)  # beta = 0
+        for dt, M, N in [(0, 9, 1), (0, 5, 5), (1, 9, 1), (2, 3, 3), (2, 17, 5), (3, 5, 9)]:
+            assert "_once_" in name(dt, M, N) and "_db" not in name(dt, M, N)
+            print(name(dt, M, N))
+            rows = 16 * int(name(dt, M, N).split("_u")[1].split("_")[0])  # of a wave
+            for e in range(20, 35):
+                for K in ((1 << e) - 1, 1 << e, (1 << e) + 1):
+                    for beta in (0.0, 1.0):
+                        assert lib.tsg_tsmm(dt, 0, K, M, N, A, M, C, N, B, N, 1.0, beta, S) == 0, (dt, M, N, K, lib.tsg_last_error())
+                        r, = launches()
+                        if not r.is_("tsmm_once"):
+                            continue
+                        assert r.grid * r.block < 1 << 32
+                        tiles = -(-K // (rows * (r.block // 64)))
+                        assert r.grid == min(tiles, ((1 << 32) - 1) // r.block), (dt, M, N, K, r.grid)
+    ''')
+    assert "_once_" in out
