@@ -241,12 +241,19 @@ __device__ __forceinline__ void block_out(const double* part, int E, int N, doub
 }
 
 // The same, and the sum over the blocks with it (TH threads; arrived null:
-// block_out).  The block that arrives last at the counter sums all slots,
-// each entry in the order of the slots over its threads' share of them and
-// then over the shares by a fixed tree, so the result does not depend on which
-// block that is; it leaves the counter at zero for the next launch.  Slots are
-// written through to memory, counted once they are there and read past the
-// caches, so that no cache is flushed or invalidated.
+// block_out).  The block that arrives last at the counter sums all slots, so
+// the result does not depend on which block that is, and leaves the counter at
+// zero for the next launch.  Slots are written through to memory, counted once
+// they are there and read past the caches, so that no cache is flushed or
+// invalidated.
+//
+// The order of the additions is fold_partials', so that a call has the same
+// bits whichever sums it: over fewer slots than that kernel has slices, a
+// halving tree, v[b] += v[b + h] for h = L/2, .., 1 over L (a power of two) of
+// them, slots past the last counting zero.  A thread has the slots of one slice
+// of S: eights of them a distance D apart are the tree's first three levels,
+// the eights then meet by halves too (taken in bit-reversed order, so that
+// neighbours meet), and the levels below S are in LDS.
 //
 // Worth it where the slots are few: one compute unit reads them, but a launch
 // is saved, which is most of a small call.
@@ -254,6 +261,7 @@ template <int CW, int TH>
 __device__ __forceinline__ void block_sum(const double* part, int E, int N, double* __restrict__ ws,
                                           double* __restrict__ C, int64_t ldc, unsigned* arrived, double* red)
 {
+    static_assert((TH & (TH - 1)) == 0, "slices and tree take a power of two of threads");
     if (!arrived) {
         block_out<CW>(part, E, N, ws, C, ldc);
         return;
@@ -272,19 +280,38 @@ __device__ __forceinline__ void block_sum(const double* part, int E, int N, doub
     int EB = 1;
     while (EB < E && EB < TH) EB <<= 1;
     const int S = TH / EB, el = threadIdx.x & (EB - 1), s = threadIdx.x / EB;
+    int m = 1;  // eights of a slice: G <= 64 slots (the host's bound), so 1, 2, 4 or 8
+    while (8 * S * m < G) m <<= 1;
+    const int D = S * m;
     for (int e0 = 0; e0 < E; e0 += EB) {
         const int e = e0 + el;
         double v = 0.0;
-        if (e < E)
-            for (int b = s; b < G; b += 8 * S) {
+        if (e < E) {
+            double pair = 0.0, four = 0.0, eight = 0.0;
+            for (int i = 0; i < m; ++i) {
+                const int b = s + S * (((i & 1) << 2 | (i & 2) | i >> 2) * m >> 3);
                 double x[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    x[u] = __hip_atomic_load(ws + (size_t)min(b + u * S, G - 1) * E + e, __ATOMIC_RELAXED,
+                    x[u] = __hip_atomic_load(ws + (size_t)min(b + u * D, G - 1) * E + e, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v += b + u * S < G ? x[u] : 0.0;
+                for (int u = 0; u < 8; ++u) x[u] = 0.0 + (b + u * D < G ? x[u] : 0.0);
+                v = ((x[0] + x[4]) + (x[2] + x[6])) + ((x[1] + x[5]) + (x[3] + x[7]));
+                if (!(i & 1)) {
+                    pair = v;
+                    continue;
+                }
+                v = pair + v;
+                if (!(i & 2)) {
+                    four = v;
+                    continue;
+                }
+                v = four + v;
+                if (!(i & 4)) eight = v;
+                else v = eight + v;
             }
+        }
         red[threadIdx.x] = v;
         __syncthreads();
         for (int h = S / 2; h >= 1; h >>= 1) {
