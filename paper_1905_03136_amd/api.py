@@ -1,16 +1,31 @@
 """torch-facing entry points.  torch supplies device memory and streams only;
 the arithmetic runs in libtsgemm's HIP kernels (see ``_lib``)."""
 import ctypes
+import warnings
 
 import torch
 
 from . import _lib
 
-try:
-    from . import _calls
-except ImportError as e:
-    raise ImportError("_calls.so is not built for this Python and torch (%s); run __graft_entry__.build() or "
-                      "python -m paper_1905_03136_amd.build" % e) from e
+
+def _load_calls():
+    """The native calls, or None if they are not built for this Python and
+    torch: the functions below then take every call themselves (10007 x 4 and 4
+    doubles: 13 us on the host instead of 4.7)."""
+    try:
+        from . import _calls
+    except ImportError as e:
+        why = e
+    else:
+        if _calls.torch_version == torch.__version__:
+            return _calls
+        why = "built for torch %s" % _calls.torch_version
+    warnings.warn("the native calls are not there for this Python and torch %s (%s), small calls take longer; run "
+                  "python -m paper_1905_03136_amd.build" % (torch.__version__, why), RuntimeWarning, stacklevel=3)
+    return None
+
+
+_calls = _load_calls()
 
 _DT = {torch.float64: _lib.TSG_R64, torch.complex128: _lib.TSG_C128,
        torch.float32: _lib.TSG_R32, torch.complex64: _lib.TSG_C64}
@@ -21,6 +36,8 @@ _SMALL = {torch.float64: torch.float64, torch.complex128: torch.complex128,
 def _bind():
     """Give the native calls the library's entry points."""
     lib = _lib.lib()
+    if _calls is None:
+        return
     _calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.tsg_tsmttsm, lib.tsg_tsmm_op)))
 
 
@@ -63,7 +80,7 @@ def tsmttsm(A, B, op="T", out=None, acc="f64"):
     binary32 over stretches of 32 rows, binary64 beyond.  ``out`` may be an
     (M x N) row-major tensor to write into.
     """
-    done = _calls.tsmttsm(A, B, op, out, acc)
+    done = _calls.tsmttsm(A, B, op, out, acc) if _calls is not None else NotImplemented
     if done is not NotImplemented:
         if type(done) is int:
             _lib.check(done)
@@ -96,7 +113,7 @@ def tsmm(A, C, out=None, alpha=1.0, beta=0.0, conjA=False, opC="N", acc="f64"):
     Writes into ``out`` (K x N, A's dtype) when given, else into a new tensor
     (beta must then be 0).  C is float64 / complex128 for every storage type.
     """
-    done = _calls.tsmm(A, C, out, alpha, beta, conjA, opC, acc)
+    done = _calls.tsmm(A, C, out, alpha, beta, conjA, opC, acc) if _calls is not None else NotImplemented
     if done is not NotImplemented:
         if type(done) is int:
             _lib.check(done)

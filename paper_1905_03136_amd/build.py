@@ -14,6 +14,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -44,8 +45,8 @@ HEADERS = [os.path.join(CSRC, h) for h in ("tsg_device.hpp", "tsg_kernels.hpp", 
 # headers of the units that hold kernels bringing their rows straight into LDS
 STAGE_HEADERS = [os.path.join(CSRC, h) for h in ("tsg_stage.hpp", "tsg_once.hpp")]
 ABI_HEADER = os.path.join(ROOT, "include", "tsgemm.h")
-# the plain calls on torch tensors, a Python extension module
-CALLS = os.path.join(HERE, "_calls.so")
+# the plain calls on torch tensors, an extension module of this Python
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 CALLS_SRC = os.path.join(CSRC, "tsg_calls.cpp")
 TUNE_LIB = os.path.join(HERE, "libtsgemm_tune.so")
 # builds of other variant sets (the autotuner's libraries): generated sources
@@ -186,12 +187,11 @@ def generate(widths=None, variants=None, gen_dir=GEN):
 def build_calls():
     """Compile the native torch calls against the installed torch (host code
     only; its addresses of libtsgemm's functions come from the loaded library)."""
-    import sysconfig
-
     import torch
     base = os.path.join(os.path.dirname(torch.__file__))
     lib = os.path.join(base, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           '-DTSG_TORCH_VERSION="%s"' % torch.__version__,
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + os.path.join(ROOT, "include"),
            "-I" + os.path.join(base, "include"),
            "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include",

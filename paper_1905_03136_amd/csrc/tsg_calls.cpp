@@ -192,4 +192,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__calls()
+{
+    PyObject* m = PyModule_Create(&module);
+    // what it was built for: another torch's tensors need not look alike
+    if (m && PyModule_AddStringConstant(m, "torch_version", TSG_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}
