@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <utility>
@@ -163,6 +164,8 @@ std::map<std::pair<int, hipStream_t>, std::mutex> g_ws_calls;  // never erased: 
 std::vector<std::pair<int, void*>> g_retired;
 // (device, variant, LDS bytes of a block) -> blocks per CU
 std::map<std::tuple<int, const tsg::Variant*, size_t>, int> g_occ;
+// (device, variant) whose kernel may ask for all of a compute unit's LDS
+std::set<std::pair<int, const tsg::Variant*>> g_lds;
 
 std::map<int, double*> g_scratch;  // device -> device address of its no-alloc scratch
 
@@ -210,16 +213,36 @@ tsg_status current_device(int* dev)
     return TSG_OK;
 }
 
+constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
+
+// Lets a kernel ask for more than the 64 KB of LDS that a block may have by
+// default: all of it, once, as its blocks' sizes vary with the widths and with
+// beta, and a smaller one must not take from a larger one (g_mu held).
+hipError_t allow_lds(int dev, const tsg::Variant& v, size_t lds)
+{
+    if (lds <= (64u << 10) || g_lds.count({dev, &v})) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(v.kernel(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    if (e == hipSuccess) g_lds.insert({dev, &v});
+    return e;
+}
+
+// The same for a call about to launch `v`.
+tsg_status lds_ready(int dev, const tsg::Variant& v, size_t lds)
+{
+    if (lds <= (64u << 10)) return TSG_OK;
+    std::lock_guard<std::mutex> lk(g_mu);
+    const hipError_t e = allow_lds(dev, v, lds);
+    return e == hipSuccess ? TSG_OK : fail(TSG_E_HIP, "%zu bytes of LDS for %s: %s", lds, v.name, hipGetErrorString(e));
+}
+
 int occupancy(int dev, const tsg::Variant& v, size_t lds)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     auto key = std::make_tuple(dev, &v, lds);
     auto it = g_occ.find(key);
     if (it != g_occ.end()) return it->second;
-    // more than the 64 KB a block may ask for by default
-    if (lds > (64u << 10))
-        hipFuncSetAttribute(v.kernel(), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int blocks = 0;
+    if (allow_lds(dev, v, lds) != hipSuccess) return 1;  // lds_ready reports it
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, v.kernel(), v.threads, lds) != hipSuccess || blocks < 1)
         blocks = 1;
     g_occ[key] = blocks;
@@ -367,8 +390,6 @@ const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda,
         if (v->stage == (sym ? 2 : 1) && v->gauss == gauss && stage_serves(*v, M, N, A, lda, B, ldb)) return v;
     return nullptr;
 }
-
-constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
 
 // LDS bytes of a block that the launch asks for (kernels with run-time sizes).
 size_t lds_for(const tsg::Variant& v, int M, int N, bool beta_nz = false)
@@ -659,6 +680,7 @@ tsg_status tsmttsm_call(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N
         calls = std::unique_lock<std::mutex>(*w.calls);
     }
     p.lds = lds_for(*v, M, N);
+    if ((s = lds_ready(dev, *v, p.lds)) != TSG_OK) return s;
     v->launch(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));
@@ -737,6 +759,7 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
     p.alpha = alpha;
     p.beta = beta;
     p.lds = lds_for(*v, M, N, beta != 0.0);
+    if ((s = lds_ready(dev, *v, p.lds)) != TSG_OK) return s;
     v->launch(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));
@@ -835,6 +858,7 @@ void tsg_finalize(void)
     }
     g_retired.clear();
     g_occ.clear();
+    g_lds.clear();
     if (cur >= 0) hipSetDevice(cur);
 }
 

@@ -63,3 +63,26 @@ def test_launch_sizes_of_long_matrices(tmp_path):
                         assert r.grid == min(tiles, ((1 << 32) - 1) // r.block), (dt, M, N, K, r.grid)
     ''')
     assert "_once_" in out
+
+
+def test_lds_of_one_kernel_by_calls_of_several_sizes(tmp_path):
+    """A kernel whose blocks take more than 64 KB of LDS, by turns more and less
+    of it (old rows read or not, narrower and wider matrices)."""
+    run(tmp_path, '''
+        big = set()
+        def sizes(call):
+            assert call() == 0, lib.tsg_last_error()
+            for r in launches():
+                if r.shmem > 64 << 10:
+                    big.add((r.name, r.shmem))
+        for turn in range(2):
+            for dt in range(4):
+                for M in range(20, 65, 3):
+                    for N in (M, 33, 48, 64):
+                        for beta in (1.0, 0.0, 1.0):
+                            sizes(lambda: lib.tsg_tsmm(dt, 0, 1 << 24, M, N, A, M, C, N, B, N, 1.0, beta, S))
+                        sizes(lambda: lib.tsg_tsmttsm(dt, 0, 1 << 24, M, N, A, M, B, N, C, N, S))
+        for kernel in ("tsmm_once", "tsmttsm_stage"):
+            names = [n for n, _ in big if kernel.encode() in n]
+            assert len(names) > len(set(names)), kernel  # of several sizes
+    ''')
