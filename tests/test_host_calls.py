@@ -86,3 +86,33 @@ def test_lds_of_one_kernel_by_calls_of_several_sizes(tmp_path):
             names = [n for n, _ in big if kernel.encode() in n]
             assert len(names) > len(set(names)), kernel  # of several sizes
     ''')
+
+
+def test_row_rule_of_the_one_tile_kernel(tmp_path):
+    """Tiles of more than 16 rows from 4096 of them on (with old rows and tiles
+    of more than 32 from 6144), of 16 rows at any length but with old rows from
+    1024 tiles; where the class's table entry takes such calls."""
+    run(tmp_path, '''
+        from paper_1905_03136_amd import codegen
+        DT = ["r64", "c128", "r32", "c64"]
+        reached = 0
+        for v in codegen.once_variants():
+            c, dt, M, N = v["cfg"], DT.index(v["dt"]), v["maxM"], v["maxN"]
+            rows = 16 * c["U"]
+            for beta, bit in ((0.0, 2), (1.0, 8)):
+                least = (6144 if beta and rows > 32 else 4096) if rows > 16 else 1024 if beta else 0
+                took = []
+                for K in (rows * least - 1, rows * least, 1 << 24):
+                    if K < 1:
+                        continue
+                    assert lib.tsg_tsmm(dt, 0, K, M, N, A, M, C, N, B, N, 1.0, beta, S) == 0
+                    r, = launches()
+                    took.append((K, r.is_("tsmm_once")))
+                if took[-1][1]:
+                    assert c["serves"] & bit
+                    assert all(once == (K >= rows * least) for K, once in took), (v, beta, took)
+                    reached += 1
+                else:
+                    assert not any(once for _, once in took)
+        assert reached > 400, reached
+    ''')
