@@ -805,11 +805,12 @@ tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stre
     if (s != TSG_OK) return s;
     DeviceInfo di;
     if ((s = device_info(dev, &di)) != TSG_OK) return s;
-    // the largest grid any TSMTTSM variant of this shape may use
+    // the largest grid any TSMTTSM variant of this shape may use, of the type
+    // or of the binary64-arithmetic one whose kernels serve it too
     size_t need = 0;
     for (int i = 0; i < tsg::kNumVariants; ++i) {
         const tsg::Variant& v = tsg::kVariants[i];
-        if (v.op != tsg::OP_TSMTTSM || v.dt != (int)dt) continue;
+        if (v.op != tsg::OP_TSMTTSM || (v.dt != (int)dt && v.dt != twin_of(dt))) continue;
         if (v.stage) {
             const int wide = M > N ? M : N, narrow = M > N ? N : M;
             if (v.maxM != (wide + 15) / 16 * 16 || v.maxN != (narrow + 3) / 4 * 4 || (v.stage == 2 && M != N)) continue;

@@ -116,3 +116,20 @@ def test_row_rule_of_the_one_tile_kernel(tmp_path):
                     assert not any(once for _, once in took)
         assert reached > 400, reached
     ''')
+
+
+def test_reserved_calls_can_be_captured(tmp_path):
+    """After tsg_reserve no call of the shape, any type and arithmetic, has to
+    grow the workspace."""
+    run(tmp_path, '''
+        stream = 100
+        for dt in range(6):
+            for M, N in [(5, 7), (16, 16), (17, 17), (20, 20), (24, 64), (30, 30), (33, 45), (64, 64)]:
+                for K in (3000, 20000, 100000, 1 << 22):
+                    stream += 1
+                    rec.rec_capturing(0)
+                    assert lib.tsg_reserve(dt, K, M, N, stream) == 0
+                    rec.rec_capturing(1)
+                    for ldb in (N, N + 1, N + 16):
+                        assert lib.tsg_tsmttsm(dt, 0, K, M, N, A, M, B, ldb, C, N, stream) == 0, (dt, M, N, K, ldb, lib.tsg_last_error())
+    ''')
