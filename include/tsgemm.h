@@ -84,7 +84,7 @@ typedef enum {
     TSG_OK = 0,
     TSG_E_ARG = 1,          /* invalid argument (sizes, strides, pointers, alignment) */
     TSG_E_UNSUPPORTED = 2,  /* valid but outside the supported range (M or N > 64)    */
-    TSG_E_NOMEM = 3,        /* workspace allocation failed or exceeds TSG_MAX_WORKSPACE */
+    TSG_E_NOMEM = 3,        /* an allocation failed, or a workspace exceeds TSG_MAX_WORKSPACE */
     TSG_E_HIP = 4,          /* a HIP runtime call failed (no device, launch failure)  */
     TSG_E_CAPTURE = 5       /* workspace must grow while the stream is being captured */
 } tsg_status;

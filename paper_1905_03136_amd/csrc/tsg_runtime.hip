@@ -113,6 +113,15 @@ thread_local std::string g_force;  // variant forced by tsg_force_variant ("" = 
 thread_local int g_grid_cap = 0;   // block cap set by tsg_set_grid_limit (0 = none)
 thread_local int g_reduction = 0;  // cross-block reduction set by tsg_set_reduction (0 = fixed-order fold)
 
+void set_error(const char* msg) noexcept
+{
+    try {
+        g_err = msg;
+    } catch (...) {
+        g_err.clear();
+    }
+}
+
 tsg_status fail(tsg_status s, const char* fmt, ...)
 {
     char buf[512];
@@ -120,8 +129,18 @@ tsg_status fail(tsg_status s, const char* fmt, ...)
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    g_err = buf;
+    set_error(buf);
     return s;
+}
+
+// What an entry point returns whose host allocation failed (the index of the
+// variants on the first call, a workspace's entry, a name): no exception
+// leaves it.
+template <class R>
+R no_memory(R r)
+{
+    set_error("host allocation failed");
+    return r;
 }
 
 constexpr int kMaxWidth = 64;
@@ -134,7 +153,7 @@ size_t orth_workspace_size(int64_t K, int32_t M, int32_t N, int32_t count);  // 
 // Error detail for tsg_last_error() from the library's other units.
 tsg_status report(tsg_status s, const char* msg)
 {
-    g_err = msg;
+    set_error(msg);
     return s;
 }
 }  // namespace tsg
@@ -513,6 +532,7 @@ tsg_status get_workspace(int dev, hipStream_t stream, size_t bytes, Workspace* o
     Workspace fresh;
     fresh.bytes = grow;
     fresh.calls = &g_ws_calls[key];
+    g_retired.reserve(g_retired.size() + 1);
     e = hipMalloc(&fresh.data, grow + 256);
     if (e != hipSuccess) return fail(TSG_E_NOMEM, "hipMalloc(%zu): %s", grow + 256, hipGetErrorString(e));
     hipLaunchKernelGGL(tsg::clear_counter, dim3(1), dim3(64), 0, stream, fresh.counter());
@@ -713,20 +733,24 @@ extern "C" {
 
 tsg_status tsg_tsmttsm(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N, const void* A, int64_t lda,
                        const void* B, int64_t ldb, void* C, int64_t ldc, void* stream)
-{
+try {
     return tsmttsm_call(dt, op, K, M, N, A, lda, B, ldb, C, ldc, stream, false);
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 tsg_status tsg_tsmttsm_noalloc(tsg_dtype dt, tsg_op op, int64_t K, int32_t M, int32_t N, const void* A,
                                int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, void* stream)
-{
+try {
     return tsmttsm_call(dt, op, K, M, N, A, lda, B, ldb, C, ldc, stream, true);
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32_t M, int32_t N, const void* A,
                        int64_t lda, const void* C, int64_t ldc, void* B, int64_t ldb, double alpha, double beta,
                        void* stream)
-{
+try {
     g_err.clear();
     if (opC != TSG_OP_N && opC != TSG_OP_T && opC != TSG_OP_C) return fail(TSG_E_ARG, "unknown opC %d", (int)opC);
     if (opC != TSG_OP_N && M >= 1 && ldc < M)
@@ -764,6 +788,8 @@ tsg_status tsg_tsmm_op(tsg_dtype dt, int32_t conjA, tsg_op opC, int64_t K, int32
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(TSG_E_HIP, "launch of %s: %s", v->name, hipGetErrorString(e));
     return TSG_OK;
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 tsg_status tsg_tsmm(tsg_dtype dt, int32_t conjA, int64_t K, int32_t M, int32_t N, const void* A, int64_t lda,
@@ -773,7 +799,7 @@ tsg_status tsg_tsmm(tsg_dtype dt, int32_t conjA, int64_t K, int32_t M, int32_t N
 }
 
 size_t tsg_workspace_size(int32_t op_kind, tsg_dtype dt, int64_t K, int32_t M, int32_t N, int32_t count)
-{
+try {
     if (op_kind == TSG_KIND_TSMM) return 0;
     if (op_kind == TSG_KIND_ORTH) return dt == TSG_R64 ? tsg::orth_workspace_size(K, M, N, count) : 0;
     if (op_kind != TSG_KIND_TSMTTSM) return 0;
@@ -793,10 +819,12 @@ size_t tsg_workspace_size(int32_t op_kind, tsg_dtype dt, int64_t K, int32_t M, i
         need = need > b ? need : b;
     }
     return need;
+} catch (...) {
+    return no_memory((size_t)0);
 }
 
 tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stream)
-{
+try {
     g_err.clear();
     if (M < 1 || N < 1 || K < 0) return fail(TSG_E_ARG, "invalid shape");
     if (M > kMaxWidth || N > kMaxWidth) return fail(TSG_E_UNSUPPORTED, "widths above %d", kMaxWidth);
@@ -820,10 +848,12 @@ tsg_status tsg_reserve(tsg_dtype dt, int64_t K, int32_t M, int32_t N, void* stre
     }
     Workspace w;
     return get_workspace(dev, static_cast<hipStream_t>(stream), need, &w);
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 tsg_status tsg_init(int32_t device)
-{
+try {
     g_err.clear();
     int n = 0;
     hipError_t e = hipGetDeviceCount(&n);
@@ -841,6 +871,8 @@ tsg_status tsg_init(int32_t device)
     s = scratch_of(device, &ws);
     if (cur != device) hipSetDevice(cur);
     return s;
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 void tsg_finalize(void)
@@ -879,7 +911,7 @@ const char* tsg_status_string(tsg_status s)
 const char* tsg_last_error(void) { return g_err.c_str(); }
 
 tsg_status tsg_force_variant(const char* name)
-{
+try {
     g_err.clear();
     if (!name || !*name) {
         g_force.clear();
@@ -891,6 +923,8 @@ tsg_status tsg_force_variant(const char* name)
             return TSG_OK;
         }
     return fail(TSG_E_ARG, "no kernel variant named %s", name);
+} catch (...) {
+    return no_memory(TSG_E_NOMEM);
 }
 
 tsg_status tsg_set_grid_limit(int32_t blocks)
@@ -914,7 +948,7 @@ int32_t tsg_variant_count(void) { return tsg::kNumVariants; }
 const char* tsg_variant_name(int32_t i) { return (i >= 0 && i < tsg::kNumVariants) ? tsg::kVariants[i].name : ""; }
 
 const char* tsg_kernel_name(int32_t op_kind, tsg_dtype dt, int32_t conj, int32_t M, int32_t N)
-{
+try {
     (void)conj;
     if (op_kind != 0 && op_kind != 1) return "";
     if (M < 1 || N < 1 || M > kMaxWidth || N > kMaxWidth) return "";
@@ -922,6 +956,8 @@ const char* tsg_kernel_name(int32_t op_kind, tsg_dtype dt, int32_t conj, int32_t
     // contiguous rows (lda = M, ldb = N), two 16-byte aligned operands
     const tsg::Variant* v = pick(op_kind, dt, M, N, buf16, M, buf16 + 16, N);
     return v ? v->name : "";
+} catch (...) {
+    return no_memory("");
 }
 
 }  // extern "C"

@@ -5,9 +5,11 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -32,6 +34,7 @@ uint64_t next_address = 1ull << 40;
 std::atomic<int> capturing{0};
 std::atomic<void (*)(const char*)> hook{nullptr};  // called after a launch ("launch") or in a capture query ("query")
 thread_local std::vector<Config> configs;
+thread_local bool out_of_memory = false;
 thread_local hipError_t last_error = hipSuccess;
 
 void call_hook(const char* where)
@@ -48,9 +51,20 @@ int count_args(const std::string& n)
 }
 }  // namespace
 
+// Host allocations, which the tests can make fail.
+void* operator new(size_t n)
+{
+    if (!out_of_memory)
+        if (void* p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 extern "C" {
 
 // ---- what the tests call
+void rec_out_of_memory(int on) { out_of_memory = on; }
 void rec_hook(void (*h)(const char*)) { hook = h; }
 void rec_capturing(int on) { capturing = on; }
 void rec_clear()

@@ -133,3 +133,22 @@ def test_reserved_calls_can_be_captured(tmp_path):
                     for ldb in (N, N + 1, N + 16):
                         assert lib.tsg_tsmttsm(dt, 0, K, M, N, A, M, B, ldb, C, N, stream) == 0, (dt, M, N, K, ldb, lib.tsg_last_error())
     ''')
+
+
+def test_no_exception_crosses_the_interface(tmp_path):
+    """A call whose host allocations fail says so and enqueues nothing; the
+    next one works."""
+    run(tmp_path, '''
+        calls = [lambda: lib.tsg_kernel_name(1, 0, 0, 5, 5), lambda: lib.tsg_workspace_size(0, 0, 1000, 5, 5, 1),
+                 lambda: lib.tsg_tsmm(0, 0, 1 << 20, 40, 48, A, 40, C, 48, B, 48, 1.0, 1.0, S),
+                 lambda: lib.tsg_tsmttsm(0, 0, 100000, 9, 5, A, 9, B, 5, C, 5, S),
+                 lambda: lib.tsg_tsmttsm_noalloc(0, 0, 100000, 9, 5, A, 9, B, 5, C, 5, S),
+                 lambda: lib.tsg_reserve(0, 100000, 64, 64, S + 1), lambda: lib.tsg_init(0)]
+        rec.rec_out_of_memory(1)
+        got = [f() for f in calls]
+        rec.rec_out_of_memory(0)
+        assert got == ["", 0] + [lib.TSG_E_NOMEM] * 5, got
+        assert not launches()
+        got = [f() for f in calls]
+        assert got[0] and got[1] and got[2:] == [0] * 5, got
+    ''')
