@@ -5,11 +5,12 @@ One step is one pass of the plain width sweep: TSMTTSM (C = A^T B) and TSMM
 (M, N) in {(1,1), (2,2), (4,4), (8,8), (16,16), (32,32), (64,64), (32,8), (8,32)}:
 36 calls on inputs already resident in HBM (seeded uniform(-1, 1) data,
 generated on the device).  The value is the sweep's algorithmic bytes per
-second (Eq. 1 of the paper: every element of A, B and C moves once); the JSON
-line also carries each call's median / min / max time over the timed steps,
-GB/s, GFLOP/s and fraction of the min(HBM, FP64) roofline, the roofline
-record of the dominant kernel, the measured FP64 rates of the chip, clocks
-and power, and the CPU oracle timed on the same sweep.  After the timed
+second (Eq. 1 of the paper: every element of A, B and C moves once).  The JSON
+line also carries each call's median time and fraction of the min(HBM, FP64)
+roofline, the roofline of the dominant kernel and the figures of the other
+legs; the whole record goes to a file (--detail): min / max times over the
+timed steps, GB/s, GFLOP/s, the measured FP64 rates of the chip, clocks and
+power, errors per result, and the CPU oracle timed on the same sweep.  After the timed
 steps (unless --no-forms) come the production forms and the other workload
 sizes: the precision form (binary32 storage, binary64 and binary32
 arithmetic, K = 2^25, with errors per result), the batched
@@ -771,8 +772,38 @@ def reduction_sweep(torch, api, inputs, dev, widths=(4, 32), Ks=(10**3, 10**4, 1
             torch.cuda.empty_cache()
 
 
+def line_of(out, detail):
+    """The printed record: what identifies the run and its figures, a few
+    kilobytes; `out` as a whole (tables, errors, notes) is in the file `detail`."""
+    line = {k: out[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                "scaling", "vs_baseline", "dtype", "data", "config", "source_hash")}
+    line["roofline"] = {k: v for k, v in out["roofline"].items()
+                        if k not in ("kernel_symbol", "timing", "per_launch", "traffic_source")}
+    line["b_s"] = {k: v for k, v in out["b_s"].items() if k != "note"}
+    # "D tsmm 8x8": [median us, fraction of the roofline]
+    line["calls"] = {"%s %s %dx%d" % (w["dtype"], w["op"], w["M"], w["N"]): [w["us"], w["roof_frac"]] for w in out["widths"]}
+    if "precision_form" in out:
+        line["speedup_vs_fp64"] = {
+            "%s %dx%d" % (r["dtype"], r["M"], r["N"]):
+                {op: [r["uniform"][op][form]["speedup_vs_fp64"] for form in ("fp32_acc64", "fp32_acc32")] for op in ("tsmttsm", "tsmm")}
+            for r in out["precision_form"]["widths"]}
+    if "batched_form" in out:
+        line["batched_form"] = {k: out["batched_form"][k] for k in ("us_persistent_graph", "us_128_launches", "us_orth_batched",
+                                                                    "speedup_vs_launches", "roof_frac_persistent")}
+    if "small_k" in out:
+        line["small_k"] = {k: out["small_k"][k] for k in ("us", "us_graph", "roof_frac_graph")}
+    if "autograd_form" in out:
+        line["autograd_form"] = {r["dtype"]: [r["forward_us"], r["backward_us"]] for r in out["autograd_form"]}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+    line["detail"] = detail
+    return json.dumps(line)
+
+
 def main():
     ap = argparse.ArgumentParser()
+    ap.add_argument("--detail", default=os.path.join(ROOT, "_build", "bench_detail.json"),
+                    help="file for the whole record (the printed line has the figures only)")
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=5)
     ap.add_argument("--warmup", type=int, default=2)
@@ -980,7 +1011,11 @@ def main():
     if a.cpu_sample > 0:
         print("[bench] timing the CPU oracle on a %d-row sample" % a.cpu_sample, file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline(a.cpu_sample)
-    print(json.dumps(out), flush=True)
+    os.makedirs(os.path.dirname(os.path.abspath(a.detail)), exist_ok=True)
+    with open(a.detail, "w") as f:
+        json.dump(out, f)
+        f.write("\n")
+    print(line_of(out, os.path.relpath(a.detail, ROOT)), flush=True)
 
 
 if __name__ == "__main__":
