@@ -829,7 +829,7 @@ __host__ __device__ inline int64_t slab_rows(int M, int N, int64_t ldv, int64_t 
 // instances with `total` bytes of input: kTargetSlabs slabs in all, one a
 // resident block, so that a small batch fills the chip (16 instances of 57 MB
 // in all: slabs of 8 MB left all but about twenty of 512 blocks idle, 0.53 ms
-// a launch, now 0.07), and at most the tuned size `most`, from which on larger
+// a launch, now 0.08), and at most the tuned size `most`, from which on larger
 // batches have more of them, up to kMaxSlabs an instance on average (each
 // instance's last slab is a partial one).
 __host__ __device__ inline int64_t slab_bytes(int64_t total, int count, int64_t most)

@@ -397,9 +397,12 @@ const tsg::Variant* pick_stage(int dt, int M, int N, const void* A, int64_t lda,
         if (M != N && wide > 48 && narrow > 8 && K < 65536) return nullptr;
         // bound by the matrix cores: squares whose products it pads by more than
         // 1.6 (17 to 19 columns) have kernels of their widths (2^20 rows of 17 x
-        // 17: 0.79 of its time; 20 x 20 1.17), and 13 to 16 columns against up
-        // to 48 that do not fill their blocks are 0.89 of it from long matrices
-        // on (15 x 23, 25 x 15, 33 x 13; at 100003 rows 1.10 to 1.18)
+        // 17: 0.79 of its time; 20 x 20 1.17).  For 13 to 16 columns against 17
+        // to 47 there are register rings in the three-product form (six real
+        // products for eight): at 2^20 and 2^22 rows 0.89 to 1.03 of its time (33
+        // x 16 0.89 and 0.96, 40 x 14 0.92 and 0.95, 17 x 16 0.93 and 0.96, 24 x 16
+        // 1.01 and 0.95, 40 x 16 1.00 and 0.96, 31 x 16 1.03 twice), at 2^19 level
+        // (0.93 to 1.05), at 2^18 1.04 to 1.10 and at 100003 rows 1.08 to 1.20
         if (M == N && 10 * padded > 16 * M * N) return nullptr;
         if (narrow > 12 && narrow <= 16 && wide <= 48 && wide % 16 && K >= (1 << 19)) return nullptr;
     }
@@ -422,8 +425,8 @@ size_t lds_for(const tsg::Variant& v, int M, int N, bool beta_nz = false)
 
 // The same for the one-tile kernel of TSMM (its tile: v.once rows): contiguous
 // rows or whole 16-byte chunks, widths that fill its slices and groups but for
-// the last (it masks no others, and a class that is not in the table was
-// slower than the kernels below, so no larger one stands in for it), tiles
+// the last (it masks no others, and a class that is not in the table was no
+// faster than the kernels below, so no larger one stands in for it), tiles
 // that fit LDS (with beta != 0 the old rows too).
 bool once_serves(const tsg::Variant& v, int M, int N, const void* A, int64_t lda, const void* B, int64_t ldb,
                  bool beta_nz)

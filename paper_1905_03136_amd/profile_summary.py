@@ -95,8 +95,8 @@ ARITH = ["SQ_INSTS_VALU_MFMA_F64", "SQ_INSTS_VALU_MFMA_MOPS_F64", "SQ_INSTS_VALU
 def arith(dirs, avg_us):
     """Per kernel: average counter values per dispatch and the executed FP64
     rates they give with the kernel's average duration `avg_us` (from the
-    trace): every FP64 matrix-core instruction the library issues is a
-    16x16x4 product (2048 flops per wave instruction), every FP64 FMA
+    trace): the matrix cores' flops from the counter of 512 of them (a 16x16x4
+    product counts four, a 4x4x4 product of four blocks one), every FP64 FMA
     128 flops per wave instruction (64 lanes), an add or multiply 64."""
     vals = {c: {} for c in ARITH}
     for d in dirs:
@@ -113,7 +113,7 @@ def arith(dirs, avg_us):
         t = avg_us.get(n)
         rec = dict(avg)
         if t:
-            mf = (avg["SQ_INSTS_VALU_MFMA_F64"] or 0) * 2048.0
+            mf = (avg["SQ_INSTS_VALU_MFMA_MOPS_F64"] or 0) * 512.0
             vf = (avg["SQ_INSTS_VALU_FMA_F64"] or 0) * 128.0 + ((avg["SQ_INSTS_VALU_ADD_F64"] or 0) +
                                                                   (avg["SQ_INSTS_VALU_MUL_F64"] or 0)) * 64.0
             rec.update(mfma_tflops=mf / (t * 1e-6) / 1e12, valu_tflops=vf / (t * 1e-6) / 1e12)
@@ -164,8 +164,8 @@ def render(rows, f_scale, w_scale, bench, roof, commands, title, dominant=True):
             "%.1f" % (r["written"] / 1e6) if r["written"] is not None else "-"))
     if any(r.get("arith") for r in rows):
         lines += ["", "FP64 arithmetic per kernel (counter pass: wave-level instruction counts per dispatch; "
-                  "executed rate = instructions x flops per instruction / trace duration; matrix core: 2048 "
-                  "flops per 16x16x4 FP64 product, vector: 128 per FMA, 64 per add or multiply):", "",
+                  "executed rate = operations / trace duration; matrix core: the counter of 512 flops (a 16x16x4 "
+                  "FP64 product counts four), vector: 128 flops per FMA, 64 per add or multiply):", "",
                   "| kernel | MFMA F64 insts | MFMA MOPS F64 | VALU FMA F64 | VALU add+mul F64 | executed MFMA TF/s "
                   "| executed VALU TF/s | MFMA busy cycles | SQ busy cycles | GRBM GUI active |",
                   "|---|---:|---:|---:|---:|---:|---:|---:|---:|---:|"]

@@ -356,9 +356,9 @@ def once_tuning_variants():
 
 
 def once_serves(dt, v, name, names):
-    """(mask, above) of a class: the calls in which its kernel is not slower than
-    the others, timed on the largest widths, one less and the smallest, for
-    beta = 0 and 1.  1: beta = 0 below the largest widths, 2: beta = 0 at
+    """(mask, above) of a class: the calls in which its kernel is at most 5% slower
+    than the others (at its largest widths 1%), timed on the largest widths, one
+    less and the smallest, for beta = 0 and 1.  1: beta = 0 below the largest widths, 2: beta = 0 at
     them, 4 and 8: beta = 1.  Where only the smallest widths are slower the
     class serves the largest two of each side."""
     import torch
