@@ -34,8 +34,8 @@ CFLAGS = [
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 
-# The kernels that bring their rows straight into LDS: FP64 matrix-core results in
-# architectural registers.  With C and D in accumulation registers a 16x16x4
+# The kernels that bring their rows straight into LDS, and the peak probes: FP64
+# matrix-core results in architectural registers.  With C and D in accumulation registers a 16x16x4
 # product takes 104 (two waves a SIMD) to 141 cycles (one) instead of 65:
 # register-only loops reach 38-52 and 77 TF/s.
 STAGE_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
@@ -232,6 +232,9 @@ def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, l
             text = f.read()
         return '#include "tsg_stage.hpp"' in text or '#include "tsg_once.hpp"' in text
 
+    def own_flags(s):
+        return STAGE_FLAGS if staged(s) or os.path.basename(s) == "tsg_stream.hip" else []
+
     def deps(s):
         return [s] + HEADERS + (STAGE_HEADERS if staged(s) else []) + ([] if s in units else [ABI_HEADER])
 
@@ -246,7 +249,7 @@ def build(widths=None, jobs=None, extra_flags=(), verbose=True, variants=None, l
             print("[build] compiling %d of %d %s for %s (%d variants), %d jobs"
                   % (len(todo), len(sources), what, ARCH, len(variants), jobs), flush=True)
         with cf.ThreadPoolExecutor(jobs) as ex:
-            for done in ex.map(lambda so: _compile(so[0], so[1], list(extra_flags) + (STAGE_FLAGS if staged(so[0]) else []),
+            for done in ex.map(lambda so: _compile(so[0], so[1], list(extra_flags) + own_flags(so[0]),
                                                        so[0] in units), todo):
                 if verbose:
                     print("[build]   %s" % os.path.relpath(done, ROOT), flush=True)

@@ -108,7 +108,9 @@ void launch_mix(int grid, hipStream_t st, const d2* x, int64_t nch, d2* y, int64
 // Register-only loops with CH independent accumulator chains per lane, so
 // that neither dependences nor memory limit the issue rate; the grid of
 // blocks_per_cu blocks of 256 threads per compute unit sets the waves per
-// SIMD.  Values stay small and normal (no denormal or overflow slow paths).
+// SIMD.  The unit is compiled with matrix-core results in architectural
+// registers: in accumulation registers the FP64 loop reaches 38 to 52 TF/s
+// instead of 77.  Values stay small and normal (no denormal or overflow slow paths).
 constexpr int kChains = 8;
 typedef double dbl4p __attribute__((ext_vector_type(4)));
 typedef float flt4p __attribute__((ext_vector_type(4)));
