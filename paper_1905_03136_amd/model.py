@@ -45,7 +45,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE1 = [(4 << 10, 2350.0), (8 << 10, 3950.0), (16 << 10, 6200.0), (32 << 10, 7100.0), (64 << 10, 7050.0),
           (256 << 10, 7000.0)]
 MIX_CEILING = {(1, 1): 5384.0, (2, 1): 5836.0, (4, 1): 5969.0, (1, 2): 5358.0, (1, 4): 5091.0}  # read:write
-P_MFMA = 54.0e12     # FP64 matrix-core flops/s (best kernel's executed rate; probe 51.5)
+P_MFMA = 54.0e12     # FP64 matrix-core flops/s (best executed rate of the kernels the model ranks)
 # fraction of P_MFMA reached with this many waves per SIMD (peak probe: one
 # wave keeps the FP64 matrix core busy 48% of the cycles, two or more 66%)
 MFMA_BY_WAVES = {1: 0.48 / 0.66, 2: 1.0}
