@@ -62,7 +62,7 @@ struct Variant {
     int once_db;  // two tiles of a wave in LDS, persistent blocks
     int once_m, once_n;  // it serves widths above these: those of the next smaller class, or nearer
     // the calls for which no other kernel was faster by more than 5% (1% at its
-    // largest widths; the timings differ by as much from box to box): 1 beta = 0,
+    // largest widths; timings differ by as much from run to run): 1 beta = 0,
     // 2 beta = 0 and its largest widths, 4 and 8 the same for beta != 0
     int once_for;
     int sums;  // TSMTTSM: takes Launch.arrived

@@ -46,8 +46,8 @@ TABLE1 = [(4 << 10, 2350.0), (8 << 10, 3950.0), (16 << 10, 6200.0), (32 << 10, 7
           (256 << 10, 7000.0)]
 MIX_CEILING = {(1, 1): 5384.0, (2, 1): 5836.0, (4, 1): 5969.0, (1, 2): 5358.0, (1, 4): 5091.0}  # read:write
 P_MFMA = 54.0e12     # FP64 matrix-core flops/s (best executed rate of the kernels the model ranks)
-# fraction of P_MFMA reached with this many waves per SIMD (peak probe: one
-# wave keeps the FP64 matrix core busy 48% of the cycles, two or more 66%)
+# fraction of P_MFMA reached with this many waves per SIMD (results in accumulation registers:
+# one wave keeps the FP64 matrix core busy 48% of the cycles, two or more 66%)
 MFMA_BY_WAVES = {1: 0.48 / 0.66, 2: 1.0}
 P_VALU = 66.0e12     # FP64 vector FMA flops/s at full occupancy (probe)
 T_LAUNCH = 6e-6      # a launch plus, for TSMTTSM, the fold of the partials
